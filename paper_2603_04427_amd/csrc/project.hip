@@ -19,6 +19,8 @@
 #include "tk_device.hpp"
 #include "tk_internal.hpp"
 
+#include <type_traits>
+
 namespace tk {
 
 namespace {
@@ -277,21 +279,179 @@ __global__ __launch_bounds__(proj_threads<BN>(), 1) void project_kernel(const Pr
     }
 }
 
+// Few output tiles (decode steps, short prompts). The tiled kernel above walks
+// all of d_model in each workgroup, k-tile after k-tile, so with few workgroups
+// its time is d_model / 32 memory round trips whatever the token count. Here the
+// output tile is small and the NW waves of a workgroup split d_model instead: a
+// wave takes every NW-th granule of two 32-wide k-steps (128 bytes of each row,
+// a cache line), copies them into a ring of D slots of its own (global->LDS, no
+// barriers: only this wave reads them) and multiplies them with 16x16x32
+// products; the waves' partial tiles are added up in LDS in wave order. The
+// copies go through LDS, although no other wave shares them, because the lanes
+// of a matrix operand hold 16 different rows side by side: loaded directly, four
+// neighbouring lanes touch four cache lines, a quarter of the L1's rate.
+template <int BN, int BM, int NW, int D>
+struct SplitTile {
+    static constexpr int kNA = BN / 16, kNB = BM / 16;  // 16-row blocks (one copy each) of weights and of tokens
+    static constexpr int kCopies = kNA + kNB;           // a lane's copies per k-step
+    static constexpr int kSlot = (BN + BM) * kPBK;      // bf16 per ring slot: weight rows, then token rows
+    static constexpr int kRow = BN + 4;                 // floats per token of a partial tile (16-byte pad)
+    static_assert((D & (D - 1)) == 0 && (D - 1) * kCopies <= 63, "ring depth");
+    union {
+        uint16_t ring[NW][D][kSlot];
+        float part[NW][BM * kRow];
+    };
+};
+
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+template <int BN, int BM, int NW, int D>
+__global__ __launch_bounds__(64 * NW, 1) void project_split_kernel(const ProjectParams p) {
+    using T = SplitTile<BN, BM, NW, D>;
+    constexpr int NA = T::kNA, NB = T::kNB;
+    __shared__ __align__(16) T sm;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r16 = lane & 15, q4 = lane >> 4;
+    const int per_xcd = (p.tiles + kXcdCount - 1) / kXcdCount;
+    const int logical = (int)(blockIdx.x % kXcdCount) * per_xcd + (int)(blockIdx.x / kXcdCount);
+    if (logical >= p.tiles) return;
+    const int n_tiles = (p.N + BN - 1) / BN;
+    const int n_base = (logical % n_tiles) * BN, m_base = (logical / n_tiles) * BM;
+
+    // Copy i of a k-step moves 16 rows of 64 bytes, four neighbouring lanes a row,
+    // into the rotated order of sw(). Weight rows past the matrix re-read its last
+    // row; token rows past it are not copied, except that lane 0 re-reads the last
+    // row, so that every copy is issued (the waits below count them). What lies in
+    // those rows feeds only outputs that are not stored.
+    const int wlast = (p.N - n_base < BN ? p.N - n_base : BN) - 1;
+    const int xrows = p.M - m_base < BM ? p.M - m_base : BM;
+    const int crow = lane >> 2, cchunk = (lane & 3) ^ ((lane >> 4) & 3);
+    const char* wg = (const char*)p.wt + (size_t)n_base * p.K * 2;
+    const char* xg = (const char*)p.x + (size_t)m_base * p.K * 2;
+    uint32_t woff[NA], xoff[NB];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) {
+        const int r = i * 16 + crow;
+        woff[i] = (uint32_t)(r < wlast ? r : wlast) * (uint32_t)p.K * 2u + cchunk * 16;
+    }
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+        const int r = j * 16 + crow;
+        xoff[j] = (uint32_t)(r < xrows ? r : xrows - 1) * (uint32_t)p.K * 2u + cchunk * 16;
+    }
+
+    // this wave's k-steps: granules wave, wave + NW, ... of two steps each
+    const int ksteps = p.K / kPBK, granules = (ksteps + 1) / 2;
+    const int mine = wave < granules ? (granules - wave + NW - 1) / NW : 0;
+    const int cnt = 2 * mine - ((ksteps & 1) && mine > 0 && wave + (mine - 1) * NW == granules - 1 ? 1 : 0);
+    auto issue = [&](int t) {
+        const int k = 2 * (wave + NW * (t >> 1)) + (t & 1);
+        const char* wk = wg + (size_t)k * (kPBK * 2);
+        const char* xk = xg + (size_t)k * (kPBK * 2);
+        uint16_t* slot = sm.ring[wave][t & (D - 1)];
+#pragma unroll
+        for (int i = 0; i < NA; ++i) copy16_to_lds(wk, woff[i], slot + i * 16 * kPBK);
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+            if (j * 16 + crow < xrows || lane == 0) copy16_to_lds(xk, xoff[j], slot + (BN + j * 16) * kPBK);
+    };
+    f32x4 acc[NA][NB];
+#pragma unroll
+    for (int i = 0; i < NA; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto step = [&](int t) {
+        const uint16_t* slot = sm.ring[wave][t & (D - 1)];
+        bf16x8 a[NA], b[NB];
+#pragma unroll
+        for (int i = 0; i < NA; ++i) a[i] = *(const bf16x8*)(slot + sw(i * 16 + r16, q4));
+#pragma unroll
+        for (int j = 0; j < NB; ++j) b[j] = *(const bf16x8*)(slot + BN * kPBK + sw(j * 16 + r16, q4));
+#pragma unroll
+        for (int i = 0; i < NA; ++i)
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+    };
+#pragma unroll
+    for (int t = 0; t < D; ++t)
+        if (t < cnt) issue(t);
+    int t = 0;
+    for (; t + D < cnt; ++t) {
+        wait_vm<(D - 1) * T::kCopies>();
+        step(t);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the slot is read before it is filled again
+        issue(t + D);
+    }
+    auto drain = [&](auto self, auto d_c) {
+        constexpr int d = decltype(d_c)::value;
+        if (t + d < cnt) {
+            wait_vm<d * T::kCopies>();
+            step(t++);
+        }
+        if constexpr (d > 0) self(self, std::integral_constant<int, d - 1>{});
+    };
+    drain(drain, std::integral_constant<int, D - 1>{});
+    __syncthreads();  // every ring is drained: the LDS becomes the partial tiles
+
+    // accumulator lane (r16, q4) of block (i, j): columns 16 i + 4 q4 .. + 3 of token 16 j + r16
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+        for (int i = 0; i < NA; ++i)
+            *(f32x4*)&sm.part[wave][(j * 16 + r16) * T::kRow + i * 16 + 4 * q4] = acc[i][j];
+    __syncthreads();
+    constexpr int GROUPS = BM * BN / 4;  // groups of four columns of one token
+    for (int e = tid; e < GROUPS; e += 64 * NW) {
+        const int ml = e / (BN / 4), nl = (e % (BN / 4)) * 4;
+        const int m = m_base + ml, n = n_base + nl;
+        f32x4 sum = *(const f32x4*)&sm.part[0][ml * T::kRow + nl];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) sum += *(const f32x4*)&sm.part[w][ml * T::kRow + nl];
+        if (m >= p.M || n >= p.N) continue;
+        const int bb = m / p.S, s = m - bb * p.S;
+        const int h = n / p.width, w = n - h * p.width;
+        uint2 v;
+        v.x = pack_bf16(sum[0], sum[1]);
+        v.y = pack_bf16(sum[2], sum[3]);
+        *(uint2*)((uint16_t*)p.y + (((size_t)bb * p.heads + h) * p.S + s) * p.width + w) = v;
+    }
+}
+
 }  // namespace
 
-// Tile shape of a call, the largest that still gives every CU a workgroup:
-// 256 x 256 (8 waves of 64 columns x 128 tokens, one workgroup per CU); else
-// 256 columns x 128 tokens (8 waves of 64 x 64), which serves the narrow
-// thin-key projection (a few KV heads of r columns) over long inputs with the
-// token rows read once; else 128 x 128 (4 waves, two workgroups per CU), so that
-// short sequences still spread over the part.
-enum class ProjShape { k256x256, k256x128, k128x128 };
+// Tile shape of a call. For many output tiles the largest that still gives every
+// CU a workgroup: 256 x 256 (8 waves of 64 columns x 128 tokens, one workgroup
+// per CU); else 256 columns x 128 tokens (8 waves of 64 x 64), which serves the
+// narrow thin-key projection (a few KV heads of r columns) over long inputs with
+// the token rows read once; else 128 x 128 (4 waves, two workgroups per CU).
+// Below that the waves split d_model over a small tile (project_split_kernel):
+// the smallest of 16 x 16, 16 x 32, 32 x 32 and 32 x 64 with which every CU has
+// at most one workgroup, since a workgroup's time grows with its columns plus
+// tokens (both are read over all of d_model) as long as CUs are free to take
+// more of them; then 64 x 64 up to two workgroups per CU, beyond which 128 x 128
+// tiles, which read half as much per output, are as fast. Measured (weights from
+// HBM, d_model 4096, N = 1024, us per call, 128 x 128 tiles against the adopted
+// shape): 16 tokens 35.1 / 6.2, 64 tokens 36.3 / 7.3, 128 tokens 36.7 / 9.7, 256
+// tokens 36.8 / 13.5, 512 tokens 38.7 / 18.5, 1024 tokens 40.2 / 22.8, 2048
+// tokens 40.8 / 40.3; 4096 tokens x 256 columns 39.1 / 21.0; d_model 768, 1024
+// tokens x 768 columns 10.7 / 6.9.
+enum class ProjShape { k256x256, k256x128, k128x128, k64x64, k32x64, k32x32, k16x32, k16x16 };
 
 static long tiles_of(long M, long N, long BN, long BM) { return ((M + BM - 1) / BM) * ((N + BN - 1) / BN); }
 
 static ProjShape shape_of(long M, long N) {
     if (tiles_of(M, N, 256, 256) >= 256) return ProjShape::k256x256;
     if (tiles_of(M, N, 256, 128) >= 256) return ProjShape::k256x128;
+    if (tiles_of(M, N, 16, 16) <= 256) return ProjShape::k16x16;
+    if (tiles_of(M, N, 16, 32) <= 256) return ProjShape::k16x32;
+    if (tiles_of(M, N, 32, 32) <= 256) return ProjShape::k32x32;
+    if (tiles_of(M, N, 32, 64) <= 256) return ProjShape::k32x64;
+    if (tiles_of(M, N, 64, 64) <= 512) return ProjShape::k64x64;
     return ProjShape::k128x128;
 }
 
@@ -299,6 +459,11 @@ long project_tiles(long M, long N) {
     switch (shape_of(M, N)) {
         case ProjShape::k256x256: return tiles_of(M, N, 256, 256);
         case ProjShape::k256x128: return tiles_of(M, N, 256, 128);
+        case ProjShape::k64x64: return tiles_of(M, N, 64, 64);
+        case ProjShape::k32x64: return tiles_of(M, N, 32, 64);
+        case ProjShape::k32x32: return tiles_of(M, N, 32, 32);
+        case ProjShape::k16x32: return tiles_of(M, N, 16, 32);
+        case ProjShape::k16x16: return tiles_of(M, N, 16, 16);
         default: return tiles_of(M, N, 128, 128);
     }
 }
@@ -312,6 +477,21 @@ tk_status launch_project(const ProjectParams& p, hipStream_t st) {
             break;
         case ProjShape::k256x128:
             hipLaunchKernelGGL((project_kernel<256, 128>), grid, dim3(ProjTile<256, 128>::kThreads), 0, st, p);
+            break;
+        case ProjShape::k64x64:
+            hipLaunchKernelGGL((project_split_kernel<64, 64, 4, 2>), grid, dim3(256), 0, st, p);
+            break;
+        case ProjShape::k32x64:
+            hipLaunchKernelGGL((project_split_kernel<32, 64, 8, 2>), grid, dim3(512), 0, st, p);
+            break;
+        case ProjShape::k32x32:
+            hipLaunchKernelGGL((project_split_kernel<32, 32, 8, 4>), grid, dim3(512), 0, st, p);
+            break;
+        case ProjShape::k16x32:
+            hipLaunchKernelGGL((project_split_kernel<16, 32, 8, 4>), grid, dim3(512), 0, st, p);
+            break;
+        case ProjShape::k16x16:
+            hipLaunchKernelGGL((project_split_kernel<16, 16, 8, 4>), grid, dim3(512), 0, st, p);
             break;
         default:
             hipLaunchKernelGGL((project_kernel<128, 128>), grid, dim3(ProjTile<128, 128>::kThreads), 0, st, p);

@@ -112,7 +112,7 @@ struct ProjectParams {
     const void* wt;  // [N = heads * width, K] bf16, the weight's columns as rows
     void* y;         // [batch, heads, S, width] bf16
     int M, N, K, S, heads, width;
-    int tiles;       // 128 x 128 output tiles
+    int tiles;       // output tiles of the shape the call takes (project_tiles)
 };
 
 long project_tiles(long M, long N);

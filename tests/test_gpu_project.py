@@ -7,9 +7,8 @@ oracle on the same seeded inputs (Sec. 2.3, Eq. 6-7).
   exact products (at most d_model * 2^-24 of sum |x||w|) and one rounding to
   bf16 (at most 2^-8 of the value):
       |Y_gpu - Y| <= 2^-8 |Y| + (1 + 2^-8) d_model 2^-24 (|X| |W|).
-  Shapes cover both tile shapes the kernel picks (128 x 128 and 256 x 256),
-  tile tails in tokens and columns, odd numbers of k-tiles, head widths 4-128
-  and a single token.
+  Shapes cover every tile shape the kernel picks, tile tails in tokens and
+  columns, odd numbers of k-tiles, head widths 4-128 and a single token.
 * The converted layer: factor.factor_layer on a layer whose key heads have exact
   rank r, then factor.project_thin (three kernel calls) against
   oracle.factored.thin_projections, which redoes the SVD with numpy in fp64.
@@ -60,6 +59,15 @@ SHAPES = [  # (B, S, d_model, heads, width)
     (1, 4100, 160, 64, 68),   # 256 x 256 tiles over an odd number (5) of k-tiles
     (1, 4096, 32, 64, 64),    # 256 x 256 tiles over a single k-tile
     (2, 16350, 288, 7, 36),   # 256 x 128 tiles (narrow and long): ragged columns and tokens, 9 k-tiles
+    # tiles whose waves split d_model (few tokens), then 128 x 128 tiles
+    (1, 1, 32, 5, 4),         # 16 x 16: a single k-step, 20 columns
+    (16, 1, 4096, 32, 32),    # 16 x 16: a decode step, one token per sequence
+    (1, 17, 96, 3, 20),       # 16 x 16: 3 k-steps, tails
+    (1, 100, 544, 33, 20),    # 16 x 32: 17 k-steps, tails
+    (1, 150, 1056, 33, 28),   # 32 x 32: 33 k-steps, tails
+    (2, 170, 288, 33, 28),    # 32 x 64: 9 k-steps, tails
+    (1, 1000, 224, 33, 28),   # 64 x 64: 7 k-steps, tails
+    (1, 2500, 160, 15, 68),   # 128 x 128: 5 k-tiles, tails
 ]
 
 
