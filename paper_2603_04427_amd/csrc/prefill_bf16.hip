@@ -10,6 +10,9 @@
 //    block; QC = 2 gives it 64 rows, each LDS operand read then feeding two
 //    MFMAs) of one query head; the workgroup covers HPW = gcd(G, 4) heads of one
 //    KV group and 4 / HPW row blocks, so each K/V tile in LDS serves every wave.
+//    Calls with too few rows to fill the part take fewer waves per tile (GW) and
+//    several key groups of such waves (KS), which walk the tiles in turn with
+//    tiles of their own and merge in LDS (the rule is above the dispatch).
 //  * 64-key tiles are double-buffered in LDS and filled straight from global
 //    memory (global_load_lds, 16 bytes per lane, issued a whole tile ahead and
 //    awaited only before the barrier that publishes the tile), K and V both in their memory
@@ -64,9 +67,30 @@ __device__ __forceinline__ int swz(int r) {
 }
 
 template <int R, int DV>
-struct Smem {
+struct Tiles {
     uint16_t k[2][kBN * R];
     uint16_t v[2][kBN * DV];
+};
+
+// What a wave of key group 1, 2, ... hands to the wave of group 0 with the same
+// rows: its output accumulators as they lie in the lanes, and its rows' reference
+// maxima and sums.
+template <int DV>
+struct Partial {
+    float4 o[DV / 8][64];
+    float m[64], l[64];
+};
+
+// GW waves share each tile; KS key groups of GW waves take the key tiles in turn,
+// each with tiles of its own. After the walk the same LDS holds the partials.
+template <int R, int DV, int GW, int KS>
+union Smem {
+    Tiles<R, DV> tiles[KS];
+    Partial<DV> part[KS > 1 ? (KS - 1) * GW : 1];
+};
+template <int R, int DV, int GW>
+union Smem<R, DV, GW, 1> {
+    Tiles<R, DV> tiles[1];
 };
 
 // Global->LDS copies of one 64-key K and V tile (global_load_lds, 16 bytes per
@@ -89,17 +113,27 @@ struct TileLanes {
     // swz<W, true> every RPL * CPR / 4
     static constexpr int KPER = ((256 / (2 * R)) > 0 ? 256 / (2 * R) : 1) * (R / 8);
     static constexpr int VPER = ((256 / (2 * DV)) > 0 ? 256 / (2 * DV) : 1) * (DV / 8) / 4;
-    static_assert(KL == 1 || KSTEP % KPER == 0, "K copy offsets are not a constant stride apart");
-    static_assert(VL == 1 || VSTEP % VPER == 0, "V copy offsets are not a constant stride apart");
-    uint32_t k_off;  // byte offset (in the tile) of this lane's first K chunk
-    uint32_t v_off;
+    // copies that lie apart by less than a swizzle period: their offsets repeat every KN (VN)
+    static constexpr int KN = KL == 1 || KSTEP % KPER == 0 ? 1 : KPER / KSTEP;
+    static constexpr int VN = VL == 1 || VSTEP % VPER == 0 ? 1 : VPER / VSTEP;
+    static_assert(KN == 1 || KPER % KSTEP == 0, "K copy offsets do not repeat");
+    static_assert(VN == 1 || VPER % VSTEP == 0, "V copy offsets do not repeat");
+    uint32_t k_off[KN];  // byte offsets (in the tile) of this lane's first K chunks
+    uint32_t v_off[VN];
     int tid_;
 
     __device__ __forceinline__ explicit TileLanes(int tid) : tid_(tid) {
-        const int kr = tid / (R / 8), kp = tid % (R / 8);
-        k_off = (uint32_t)((kr * R + (kp ^ swz<R, false>(kr)) * 8) * 2);
-        const int vr = tid / (DV / 8), vp = tid % (DV / 8);
-        v_off = (uint32_t)((vr * DV + (vp ^ swz<DV, true>(vr)) * 8) * 2);
+        const int kp = tid % (R / 8), vp = tid % (DV / 8);
+#pragma unroll
+        for (int j = 0; j < KN; ++j) {
+            const int kr = tid / (R / 8) + j * KSTEP;
+            k_off[j] = (uint32_t)((kr * R + (kp ^ swz<R, false>(kr)) * 8) * 2);
+        }
+#pragma unroll
+        for (int j = 0; j < VN; ++j) {
+            const int vr = tid / (DV / 8) + j * VSTEP;
+            v_off[j] = (uint32_t)((vr * DV + (vp ^ swz<DV, true>(vr)) * 8) * 2);
+        }
     }
     // tile rows of the chunks, recomputed (needed only for a ragged last tile)
     __device__ __forceinline__ int k_row(int i) const { return (tid_ + i * NT) / (R / 8); }
@@ -122,12 +156,14 @@ __device__ __forceinline__ void load_tile(const TileLanes<R, DV, NT>& tl, uint16
 #pragma unroll
         for (int i = 0; i < T::KL; ++i) {
             if (T::KC % NT != 0 && wave_base + i * NT >= T::KC) break;
-            copy16_to_lds(kt + i * T::KSTEP * R * 2, tl.k_off, ks + (wave_base + i * NT) * 8);
+            copy16_to_lds(kt + (i - i % T::KN) * T::KSTEP * R * 2, tl.k_off[i % T::KN],
+                          ks + (wave_base + i * NT) * 8);
         }
 #pragma unroll
         for (int i = 0; i < T::VL; ++i) {
             if (T::VC % NT != 0 && wave_base + i * NT >= T::VC) break;
-            copy16_to_lds(vt + i * T::VSTEP * DV * 2, tl.v_off, vs + (wave_base + i * NT) * 8);
+            copy16_to_lds(vt + (i - i % T::VN) * T::VSTEP * DV * 2, tl.v_off[i % T::VN],
+                          vs + (wave_base + i * NT) * 8);
         }
         return;
     }
@@ -144,7 +180,7 @@ __device__ __forceinline__ void load_tile(const TileLanes<R, DV, NT>& tl, uint16
     for (int i = 0; i < T::KL; ++i) {
         if (T::KC % NT != 0 && wave_base + i * NT >= T::KC) break;
         const int kr = tl.k_row(i);
-        const uint32_t oi = tl.k_off + (uint32_t)(i * T::KSTEP * R * 2);
+        const uint32_t oi = tl.k_off[i % T::KN] + (uint32_t)((i - i % T::KN) * T::KSTEP * R * 2);
         const uint32_t off = kr > last ? oi - (uint32_t)((kr - last) * R * 2) : oi;
         copy16_to_lds(kt, off, ks + (wave_base + i * NT) * 8);
     }
@@ -152,7 +188,7 @@ __device__ __forceinline__ void load_tile(const TileLanes<R, DV, NT>& tl, uint16
     for (int i = 0; i < T::VL; ++i) {
         if (T::VC % NT != 0 && wave_base + i * NT >= T::VC) break;
         const int vr = tl.v_row(i);
-        const uint32_t oi = tl.v_off + (uint32_t)(i * T::VSTEP * DV * 2);
+        const uint32_t oi = tl.v_off[i % T::VN] + (uint32_t)((i - i % T::VN) * T::VSTEP * DV * 2);
         const uint32_t off = vr > last ? oi - (uint32_t)((vr - last) * DV * 2) : oi;
         copy16_to_lds(vt, off, vs + (wave_base + i * NT) * 8);
     }
@@ -204,22 +240,33 @@ __device__ __forceinline__ bf16x8 vt_operand(const uint16_t* vs, uint32_t vbase,
 
 }  // namespace
 
-// QC: 32-query column blocks per wave (1 or 2); NW: waves per workgroup.
-template <int R, int DV, int QC, int NW>
-__global__ __launch_bounds__(64 * NW, QC == 1 ? (R <= 32 ? 3 : 2) : 1) void prefill_bf16_kernel(const PrefillParams p,
-                                                                                     int n_groups) {
+// Waves of a workgroup that share each K/V tile and split heads and rows (GW), and
+// key groups of such waves (KS).
+constexpr int prefill_min_blocks(int R, int QC, int KS) { return KS > 1 ? 1 : QC == 1 ? (R <= 32 ? 3 : 2) : 1; }
+
+// Heads of a KV group per workgroup: as many of gcd(G, 4) as its GW waves hold.
+__host__ __device__ constexpr int heads_per_group(int G, int GW) { return gcd4(G) < GW ? gcd4(G) : GW; }
+
+// QC: 32-query column blocks per wave (1 or 2).
+template <int R, int DV, int QC, int GW, int KS>
+__global__ __launch_bounds__(64 * GW * KS, prefill_min_blocks(R, QC, KS)) void prefill_bf16_kernel(
+    const PrefillParams p, int n_groups) {
     constexpr int KSTEPS = R / 16;  // MFMA K-steps of the score product
     constexpr int DBLK = DV / 32;   // 32-row blocks of O^T
-    constexpr int NT = 64 * NW;
-    __shared__ Smem<R, DV> sm;
+    constexpr int NT = 64 * GW;     // threads that fill one tile
+    static_assert(KS == 1 || QC == 1, "key groups take one query block per wave");
+    __shared__ Smem<R, DV, GW, KS> smem;
 
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = threadIdx.x & 63, all_wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = KS == 1 ? all_wave : all_wave % GW;  // wave of its key group
+    const int kgrp = KS == 1 ? 0 : all_wave / GW;
+    const int tid = KS == 1 ? (int)threadIdx.x : wave * 64 + lane;  // thread of its key group
     const int half = lane >> 5, col = lane & 31;
+    Tiles<R, DV>& sm = smem.tiles[kgrp];
 
     // ---- workgroup -> (KV sequence, query block), XCD-aware and heaviest first
-    const int HPW = gcd4(p.G);
-    const int RB = NW / HPW;
+    const int HPW = heads_per_group(p.G, GW);
+    const int RB = GW / HPW;
     const int BM = 32 * QC * RB;
     const int nqb = (p.Sq + BM - 1) / BM;
     const int per_xcd = (n_groups + kXcds - 1) / kXcds;
@@ -247,8 +294,10 @@ __global__ __launch_bounds__(64 * NW, QC == 1 ? (R <= 32 ? 3 : 2) : 1) void pref
         key_end = last < key_end ? last : key_end;
     }
     const int ntiles = (key_end + kBN - 1) / kBN;
+    // this key group's tiles: kgrp, kgrp + KS, ...; every group passes the same barriers
+    const int nsteps = (ntiles + KS - 1) / KS;
     const TileLanes<R, DV, NT> tl(tid);
-    load_tile<R, DV, NT>(tl, sm.k[0], sm.v[0], kg, vg, 0, p.Sk, wave);
+    if (KS == 1 || kgrp < ntiles) load_tile<R, DV, NT>(tl, sm.k[0], sm.v[0], kg, vg, kgrp * kBN, p.Sk, wave);
 
     // Q^T operands: column block qc holds query rows qw0 + 32 qc + col, dims 16m + 8 half .. +7
     bf16x8 qreg[QC][KSTEPS];
@@ -320,10 +369,13 @@ __global__ __launch_bounds__(64 * NW, QC == 1 ? (R <= 32 ? 3 : 2) : 1) void pref
     // immediate offsets
     auto tile_step = [&](auto cur_c, int t) {
         constexpr int cur = decltype(cur_c)::value;
-        const int base = t * kBN;
-        if (t + 1 < ntiles) load_tile<R, DV, NT>(tl, sm.k[cur ^ 1], sm.v[cur ^ 1], kg, vg, base + kBN, p.Sk, wave);
+        const int tile = KS == 1 ? t : t * KS + kgrp;
+        const int base = tile * kBN;
+        const bool more = tile + KS < ntiles;
+        if (more) load_tile<R, DV, NT>(tl, sm.k[cur ^ 1], sm.v[cur ^ 1], kg, vg, base + KS * kBN, p.Sk, wave);
 
-        if (base <= wave_last_key) {
+        // (past the last tile of a key group base is beyond every visible key)
+        if (base <= wave_last_key && (KS == 1 || tile < ntiles)) {
             const uint16_t* ks = sm.k[cur];
             const uint16_t* vs = sm.v[cur];
             // ---- S^T = K Q^T: two 32-key blocks x two query blocks
@@ -390,6 +442,12 @@ __global__ __launch_bounds__(64 * NW, QC == 1 ? (R <= 32 ? 3 : 2) : 1) void pref
                         for (int v = 0; v < 16; ++v) o[qc][d][v] *= alpha;
                 }
             }
+            // a row that has seen no visible key yet (a key group's first tiles can
+            // lie past a row's causal limit) has only -inf scores here: against 0
+            // instead of its reference they weigh 0 and not NaN
+            float m_use[QC];
+#pragma unroll
+            for (int qc = 0; qc < QC; ++qc) m_use[qc] = KS > 1 && m_ref[qc] == -INFINITY ? 0.f : m_ref[qc];
             // ---- probabilities and O^T += V^T P^T, k-step by k-step. Each V^T operand
             // is read once for both query blocks, one k-step ahead; within a k-step
             // the matrix operations of query block 0 are interleaved with the
@@ -398,7 +456,7 @@ __global__ __launch_bounds__(64 * NW, QC == 1 ? (R <= 32 ? 3 : 2) : 1) void pref
             bf16x8 va[DBLK];
 #pragma unroll
             for (int d = 0; d < DBLK; ++d) va[d] = vt_operand<DV>(vs, vaddr[d], 0);
-            bf16x8 p0 = prob_step<!MSUM>(s[0], 0, m_ref[0], c, lsum[0]);
+            bf16x8 p0 = prob_step<!MSUM>(s[0], 0, m_use[0], c, lsum[0]);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 __builtin_amdgcn_sched_barrier(0);
@@ -408,9 +466,9 @@ __global__ __launch_bounds__(64 * NW, QC == 1 ? (R <= 32 ? 3 : 2) : 1) void pref
                     for (int d = 0; d < DBLK; ++d) vb[d] = vt_operand<DV>(vs, vaddr[d], q + 1);
                 }
                 bf16x8 p1 = p0;
-                if constexpr (QC == 2) p1 = prob_step(s[QC - 1], q, m_ref[QC - 1], c, lsum[QC - 1]);
+                if constexpr (QC == 2) p1 = prob_step(s[QC - 1], q, m_use[QC - 1], c, lsum[QC - 1]);
                 bf16x8 p0n = p0;
-                if (q < 3) p0n = prob_step<!MSUM>(s[0], q + 1, m_ref[0], c, lsum[0]);
+                if (q < 3) p0n = prob_step<!MSUM>(s[0], q + 1, m_use[0], c, lsum[0]);
 #pragma unroll
                 for (int d = 0; d < DBLK; ++d)
                     o[0][d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[d], p0, o[0][d], 0, 0, 0);
@@ -435,28 +493,81 @@ __global__ __launch_bounds__(64 * NW, QC == 1 ? (R <= 32 ? 3 : 2) : 1) void pref
             }
         }
 
-        if (t + 1 < ntiles) wait_loads();  // this wave's part of the next tile has landed
+        if (more) wait_loads();  // this wave's part of the next tile has landed
         __syncthreads();
     };
     int t = 0;
-    for (; t + 1 < ntiles; t += 2) {
+    for (; t + 1 < nsteps; t += 2) {
         tile_step(std::integral_constant<int, 0>{}, t);
         tile_step(std::integral_constant<int, 1>{}, t + 1);
     }
-    if (t < ntiles) tile_step(std::integral_constant<int, 0>{}, t);
+    if (t < nsteps) tile_step(std::integral_constant<int, 0>{}, t);
+
+    // ---- row sums
+    float lrow[QC];
+#pragma unroll
+    for (int qc = 0; qc < QC; ++qc) {
+        if constexpr (MSUM) {
+            const float a0 = __shfl(lacc[0], col & 15);
+            const float a1 = __shfl(lacc[1], col & 15);
+            lrow[qc] = col < 16 ? a0 : a1;
+        } else {
+            lrow[qc] = xor32_sum(lsum[qc]);
+        }
+    }
+
+    // ---- key groups: the waves of group 0 merge the others' partials of their
+    // rows, in group order, with the log-sum-exp rule. A partial keeps its place
+    // in the lanes, so it is written and read 16 bytes per lane without conflicts.
+    // (A group that saw no key of a row has reference -inf and zero sums: its
+    // factor is 0. The last barrier of the walk has freed the tiles.)
+    if constexpr (KS > 1) {
+        if (kgrp > 0) {
+            Partial<DV>& w = smem.part[(kgrp - 1) * GW + wave];
+#pragma unroll
+            for (int d = 0; d < DBLK; ++d)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    w.o[4 * d + j][lane] =
+                        make_float4(o[0][d][4 * j], o[0][d][4 * j + 1], o[0][d][4 * j + 2], o[0][d][4 * j + 3]);
+            w.m[lane] = m_ref[0];
+            w.l[lane] = lrow[0];
+        }
+        __syncthreads();
+        if (kgrp > 0) return;
+        float M = m_ref[0];
+#pragma unroll
+        for (int k = 1; k < KS; ++k) M = max_f(M, smem.part[(k - 1) * GW + wave].m[lane]);
+        const float f0 = exp2_fast(m_ref[0] - M);
+        m_ref[0] = M;
+        lrow[0] *= f0;
+#pragma unroll
+        for (int d = 0; d < DBLK; ++d)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) o[0][d][v] *= f0;
+#pragma unroll 1
+        for (int k = 1; k < KS; ++k) {
+            const Partial<DV>& w = smem.part[(k - 1) * GW + wave];
+            const float f = exp2_fast(w.m[lane] - M);
+            lrow[0] = fmaf(f, w.l[lane], lrow[0]);
+#pragma unroll
+            for (int d = 0; d < DBLK; ++d)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float4 x = w.o[4 * d + j][lane];
+                    o[0][d][4 * j] = fmaf(f, x.x, o[0][d][4 * j]);
+                    o[0][d][4 * j + 1] = fmaf(f, x.y, o[0][d][4 * j + 1]);
+                    o[0][d][4 * j + 2] = fmaf(f, x.z, o[0][d][4 * j + 2]);
+                    o[0][d][4 * j + 3] = fmaf(f, x.w, o[0][d][4 * j + 3]);
+                }
+        }
+    }
 
     // ---- epilogue: normalise and store bf16 rows (and, when asked, the row's
     // log-sum-exp: the reference maximum plus log2 of the sum, in natural log)
 #pragma unroll
     for (int qc = 0; qc < QC; ++qc) {
-        float ltot;
-        if constexpr (MSUM) {
-            const float a0 = __shfl(lacc[0], col & 15);
-            const float a1 = __shfl(lacc[1], col & 15);
-            ltot = col < 16 ? a0 : a1;
-        } else {
-            ltot = xor32_sum(lsum[qc]);
-        }
+        const float ltot = lrow[qc];
         const float inv = 1.f / ltot;
         const int qrow = qw0 + 32 * qc + col;
         if (p.lse != nullptr && half == 0 && qrow < p.Sq)
@@ -476,29 +587,63 @@ __global__ __launch_bounds__(64 * NW, QC == 1 ? (R <= 32 ? 3 : 2) : 1) void pref
     }
 }
 
-template <int R, int DV, int QC, int NW>
+template <int R, int DV, int GW, int KS>
 static hipError_t run(const PrefillParams& p, hipStream_t st) {
-    const int HPW = gcd4(p.G);
-    const int BM = 32 * QC * (NW / HPW);
+    const int HPW = heads_per_group(p.G, GW);
+    const int BM = 32 * (GW / HPW);
     const long nqb = (p.Sq + BM - 1) / BM;
     const long groups = nqb * p.Hkv * (p.G / HPW) * p.B;
     const long launched = (groups + kXcds - 1) / kXcds * kXcds;
     if (launched > 0x7fffffffL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((prefill_bf16_kernel<R, DV, QC, NW>), dim3((unsigned)launched), dim3(64 * NW), 0, st, p,
+    hipLaunchKernelGGL((prefill_bf16_kernel<R, DV, 1, GW, KS>), dim3((unsigned)launched), dim3(64 * GW * KS), 0, st, p,
                        (int)groups);
     return hipGetLastError();
 }
 
-#ifndef TK_PREFILL_QC
-#define TK_PREFILL_QC 1
-#endif
-#ifndef TK_PREFILL_WAVES
-#define TK_PREFILL_WAVES 4
-#endif
-
+// Workgroup shape of a call. A unit is one wave's rows: 32 query rows of one head.
+// With four units per workgroup and one wave per unit, a call of few units leaves
+// CUs idle and gives a busy CU's SIMDs one wave each, which exposes the tile's
+// dependent score -> softmax -> value chain (0.9 us per 64-key tile against 0.35
+// with three waves per SIMD). Key groups split that walk; fewer waves per tile
+// spread the units over more CUs, at the price of more tile copies:
+//   up to 256 units    one unit per workgroup, as many key groups as the LDS holds (up to 4)
+//   up to 512          two units, as many key groups (up to 4)
+//   up to 1024         two units x 2 where two workgroups share a CU's LDS
+//                      (r + d_v <= 160); else, and where every row walks about the
+//                      same number of keys (no causal ramp to balance) over wide
+//                      values, so that sharing the tiles counts, four units x 2
+//   up to 2048         the same where the walks are long (16 tiles or more), but
+//                      four units x 1 for the rows of equal walks
+//   up to 3072         two units x 2 for d_v 64 (three workgroups per CU) and long walks
+//   beyond             four units, one key group
+// A walk of one tile has nothing to split, and one of two or three tiles is split
+// in two at most. Measured, us per call, four units x 1 against the adopted shape
+// (r 32, d_v 128 unless stated; 32 query heads over 8 KV heads):
+//   128 queries over 8192 keys     111.6 / 44.3      500 over 7700     109.3 / 52.3
+//   1000 over 8000                 112.4 / 90.6      1024 causal        19.9 / 17.3
+//   2048 causal                     36.9 / 34.2      r 128, 500 over 7700  145.4 / 91.7
+//   12 heads, r 16, d_v 64: 1024 causal 14.0 / 9.0; 4 x 2048 causal 47.0 / 33.0
+// and, on the other side of the lines, 2 x 700 causal 18.1 against 18.8 with two
+// units x 2, 2000 over 8000 155.6 / 165.6, 8 x 2048 causal 210.6 / 238.3.
 template <int R, int DV>
 static hipError_t run(const PrefillParams& p, hipStream_t st) {
-    return run<R, DV, TK_PREFILL_QC, TK_PREFILL_WAVES>(p, st);
+    constexpr int kGroupLds = (int)sizeof(Tiles<R, DV>);
+    constexpr int kMost = 160 * 1024 / kGroupLds < 4 ? 160 * 1024 / kGroupLds : 4;  // key groups in one CU's LDS
+    constexpr bool kPair = 4 * kGroupLds <= 160 * 1024;  // two workgroups of two key groups share a CU
+    const long units = (long)p.B * p.Hq * ((p.Sq + 31) / 32);
+    const long tiles = ((long)p.Sk + kBN - 1) / kBN;
+    const bool even = !p.causal || p.Sk - p.Sq >= p.Sq;  // every row walks about as many keys
+    if (tiles >= 2) {
+        if (units <= 512 && tiles < 4) return run<R, DV, 2, 2>(p, st);
+        if (units <= 256) return run<R, DV, 1, kMost>(p, st);
+        if (units <= 512) return run<R, DV, 2, kMost>(p, st);
+        if (kPair && (DV == 64 || !even)) {
+            if (units <= 1024 || (tiles >= 16 && units <= (DV == 64 ? 3072 : 2048))) return run<R, DV, 2, 2>(p, st);
+        } else if (units <= 1024 ? tiles >= 8 : units <= 2048 && tiles >= 16 && !even) {
+            return run<R, DV, 4, 2>(p, st);
+        }
+    }
+    return run<R, DV, 4, 1>(p, st);
 }
 
 template <int R>

@@ -55,6 +55,24 @@ def test_shapes_and_masks(dtype, shape):
     gate(out, ref, dtype, str(spec))
 
 
+@pytest.mark.parametrize("r,dv", [(16, 64), (32, 128), (64, 64), (64, 128), (128, 128)])
+@pytest.mark.parametrize("shape", [
+    (1, 6, 2, 1050, 1050, True),   # 198 units of 32 rows: one unit per workgroup, G = 3, a ragged 17th tile
+    (1, 4, 1, 130, 190, False),    # 3 tiles: split in two at most
+    (5, 20, 5, 70, 300, True),     # 300 units over a prefix: two per workgroup, key groups without a fifth tile
+    (9, 20, 5, 90, 530, True),     # 540 units, rows of equal walks: four units x 2 for wide values
+    (9, 20, 5, 90, 100, True),     # 540 units, 2 tiles
+    (4, 12, 12, 700, 1030, True),  # 1056 units on a causal ramp of 17 tiles
+], ids=lambda s: "x".join(map(str, s)))
+def test_workgroup_shapes(shape, r, dv):
+    """The bf16 workgroup shapes for few rows (waves per tile x key groups), every output."""
+    B, Hq, Hkv, Sq, Sk, causal = shape
+    spec = with_shape(BASE, config_id=750 + r, batch=B, h_q=Hq, h_kv=Hkv, seq_q=Sq, seq_k=Sk, causal=causal, r=r, d_v=dv)
+    for structured in (False, True):
+        out, ref = run_full(spec, structured)
+        gate(out, ref, "bf16", f"{spec} structured={structured}")
+
+
 def test_gpt2_prefill_f32_full():
     """GPT-2 small shape, fp32, every output against the oracle (gate 1e-4)."""
     spec = WORKLOADS["gpt2_prefill_f32"]
