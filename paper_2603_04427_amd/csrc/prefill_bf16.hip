@@ -32,9 +32,8 @@
 //    each bf16 P^T operand adds up exactly the rounded probabilities that feed
 //    the value product, in place of 16 vector dot products per tile.
 //  * Causal masking only on tiles that cross a wave's diagonal; tiles above it
-//    are skipped. Workgroups are ordered so that the query blocks of one KV
-//    sequence run together on one XCD (its K/V stays in that XCD's L2),
-//    heaviest (longest causal prefix) first.
+//    are skipped. Workgroups are ordered heaviest (longest causal prefix) first
+//    over all KV sequences, and the query blocks of one sequence run on one XCD.
 #include "tk_device.hpp"
 #include "tk_internal.hpp"
 
@@ -47,7 +46,6 @@ namespace tk {
 namespace {
 
 constexpr int kBN = 64;  // keys per tile
-constexpr int kXcds = 8;
 
 __host__ __device__ constexpr int gcd4(int g) { return (g % 4 == 0) ? 4 : (g % 2 == 0 ? 2 : 1); }
 
@@ -250,7 +248,7 @@ __host__ __device__ constexpr int heads_per_group(int G, int GW) { return gcd4(G
 // QC: 32-query column blocks per wave (1 or 2).
 template <int R, int DV, int QC, int GW, int KS>
 __global__ __launch_bounds__(64 * GW * KS, prefill_min_blocks(R, QC, KS)) void prefill_bf16_kernel(
-    const PrefillParams p, int n_groups) {
+    const PrefillParams p) {
     constexpr int KSTEPS = R / 16;  // MFMA K-steps of the score product
     constexpr int DBLK = DV / 32;   // 32-row blocks of O^T
     constexpr int NT = 64 * GW;     // threads that fill one tile
@@ -264,17 +262,20 @@ __global__ __launch_bounds__(64 * GW * KS, prefill_min_blocks(R, QC, KS)) void p
     const int half = lane >> 5, col = lane & 31;
     Tiles<R, DV>& sm = smem.tiles[kgrp];
 
-    // ---- workgroup -> (KV sequence, query block), XCD-aware and heaviest first
+    // ---- workgroup -> (KV sequence, query block): the heaviest (longest prefix)
+    // block of every sequence, then the next heaviest, so that the last workgroups
+    // to start are the lightest of all; with a multiple of 8 sequences the
+    // round-robin dispatch keeps each on one XCD. (Sequence by sequence within each
+    // XCD took 191 against 177 us at 2 x 4096 tokens, 32 heads over 8, 46 against
+    // 32 us at 4 x 2048, 12 heads, d_v 64, and the same 1.31 ms at 4 x 8192.)
     const int HPW = heads_per_group(p.G, GW);
     const int RB = GW / HPW;
     const int BM = 32 * QC * RB;
     const int nqb = (p.Sq + BM - 1) / BM;
-    const int per_xcd = (n_groups + kXcds - 1) / kXcds;
-    const int logical = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
-    if (logical >= n_groups) return;
-    const int pair = logical / nqb, rank = logical % nqb;
-    const int qb = p.causal ? nqb - 1 - rank : rank;
     const int groups_per_kv = p.G / HPW;
+    const int pairs = p.B * p.Hkv * groups_per_kv;
+    const int pair = (int)(blockIdx.x % (unsigned)pairs), rank = (int)(blockIdx.x / (unsigned)pairs);
+    const int qb = p.causal ? nqb - 1 - rank : rank;
     const int b = pair / (p.Hkv * groups_per_kv);
     const int gy = pair % (p.Hkv * groups_per_kv);
     const int g = gy / groups_per_kv;
@@ -593,10 +594,8 @@ static hipError_t run(const PrefillParams& p, hipStream_t st) {
     const int BM = 32 * (GW / HPW);
     const long nqb = (p.Sq + BM - 1) / BM;
     const long groups = nqb * p.Hkv * (p.G / HPW) * p.B;
-    const long launched = (groups + kXcds - 1) / kXcds * kXcds;
-    if (launched > 0x7fffffffL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((prefill_bf16_kernel<R, DV, 1, GW, KS>), dim3((unsigned)launched), dim3(64 * GW * KS), 0, st, p,
-                       (int)groups);
+    if (groups > 0x7fffffffL) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((prefill_bf16_kernel<R, DV, 1, GW, KS>), dim3((unsigned)groups), dim3(64 * GW * KS), 0, st, p);
     return hipGetLastError();
 }
 
@@ -608,23 +607,24 @@ static hipError_t run(const PrefillParams& p, hipStream_t st) {
 // spread the units over more CUs, at the price of more tile copies:
 //   up to 256 units    one unit per workgroup, as many key groups as the LDS holds (up to 4)
 //   up to 512          two units, as many key groups (up to 4)
-//   up to 1024         two units x 2 where two workgroups share a CU's LDS
-//                      (r + d_v <= 160); else, and where every row walks about the
-//                      same number of keys (no causal ramp to balance) over wide
-//                      values, so that sharing the tiles counts, four units x 2
-//   up to 2048         the same where the walks are long (16 tiles or more), but
-//                      four units x 1 for the rows of equal walks
-//   up to 3072         two units x 2 for d_v 64 (three workgroups per CU) and long walks
+//   up to 1280         two units x 2 where two workgroups share a CU's LDS
+//                      (r + d_v <= 160); else, and up to 1024 units where every row
+//                      walks about the same number of keys (no causal ramp to
+//                      balance) over wide values, so that sharing the tiles
+//                      counts, four units x 2
+//   up to 1536         two units x 2 for d_v 64 (three workgroups per CU)
+//   up to 2048         as up to 1280 for long walks on a causal ramp (20 tiles or more)
 //   beyond             four units, one key group
 // A walk of one tile has nothing to split, and one of two or three tiles is split
 // in two at most. Measured, us per call, four units x 1 against the adopted shape
 // (r 32, d_v 128 unless stated; 32 query heads over 8 KV heads):
-//   128 queries over 8192 keys     111.6 / 44.3      500 over 7700     109.3 / 52.3
-//   1000 over 8000                 112.4 / 90.6      1024 causal        19.9 / 17.3
-//   2048 causal                     36.9 / 34.2      r 128, 500 over 7700  145.4 / 91.7
-//   12 heads, r 16, d_v 64: 1024 causal 14.0 / 9.0; 4 x 2048 causal 47.0 / 33.0
-// and, on the other side of the lines, 2 x 700 causal 18.1 against 18.8 with two
-// units x 2, 2000 over 8000 155.6 / 165.6, 8 x 2048 causal 210.6 / 238.3.
+//   128 queries over 8192 keys     111.6 / 44.3      500 over 7700     103.4 / 52.6
+//   1000 over 8000                 107.5 / 90.1      1100 causal        21.0 / 15.4
+//   2048 causal                     36.9 / 35.4      r 128, 500 over 7700  145.4 / 91.7
+//   12 heads, r 32, d_v 64: 2 x 500 causal 9.6 / 7.0; 4096 causal 48.9 / 32.9
+// and, on the other side of the lines, 2 x 1024 causal 22.2 against 23.4 with two
+// units x 2, 2000 over 8000 158 / 170, 4 x 512 causal 15.1 / 17.2; 8 x 1000 causal,
+// 12 heads, d_v 64, 21.2 / 21.7 (r 64: 23.9 / 28.7).
 template <int R, int DV>
 static hipError_t run(const PrefillParams& p, hipStream_t st) {
     constexpr int kGroupLds = (int)sizeof(Tiles<R, DV>);
@@ -637,11 +637,9 @@ static hipError_t run(const PrefillParams& p, hipStream_t st) {
         if (units <= 512 && tiles < 4) return run<R, DV, 2, 2>(p, st);
         if (units <= 256) return run<R, DV, 1, kMost>(p, st);
         if (units <= 512) return run<R, DV, 2, kMost>(p, st);
-        if (kPair && (DV == 64 || !even)) {
-            if (units <= 1024 || (tiles >= 16 && units <= (DV == 64 ? 3072 : 2048))) return run<R, DV, 2, 2>(p, st);
-        } else if (units <= 1024 ? tiles >= 8 : units <= 2048 && tiles >= 16 && !even) {
-            return run<R, DV, 4, 2>(p, st);
-        }
+        const bool ramp = !even && (units <= 1280 || (units <= 2048 && tiles >= 20));
+        if (kPair && (DV == 64 ? units <= 1536 : ramp)) return run<R, DV, 2, 2>(p, st);
+        if (!(kPair && DV == 64) && tiles >= 8 && (ramp || units <= 1024)) return run<R, DV, 4, 2>(p, st);
     }
     return run<R, DV, 4, 1>(p, st);
 }

@@ -36,11 +36,13 @@ namespace tk {
 
 namespace {
 
-constexpr int kT = 64;  // keys (dq kernel) or query rows (dk/dv kernel) per LDS tile
+constexpr int kT = 64;  // keys (dq kernel) or query rows (dk/dv kernel, or half as many) per LDS tile
 constexpr int kXcds = 8;
-constexpr int kThreads = 256;
 
 __host__ __device__ constexpr int gcd4(int g) { return (g % 4 == 0) ? 4 : (g % 2 == 0 ? 2 : 1); }
+
+// Heads of a KV group per workgroup: as many of gcd(G, 4) as its GW waves hold.
+__host__ __device__ constexpr int heads_per_group(int G, int GW) { return gcd4(G) < GW ? gcd4(G) : GW; }
 
 typedef short v4s __attribute__((ext_vector_type(4)));
 
@@ -103,40 +105,72 @@ __device__ __forceinline__ bf16x8 tr_operand(const uint16_t* tile, int r0, int c
     return a;
 }
 
-// This wave's share of the global->LDS copies of a 64-row tile of width W
-// (16-byte chunks; chunk i * 256 + 64 wave + lane of the tile for copy i of a
-// lane). LDS chunk (r, pos) receives global chunk (r, pos ^ swz(r)), which is the
-// swizzled layout the reads expect. Rows at or past `rows` re-read row rows - 1:
-// finite values, masked later.
-template <int W>
+// This wave's share of the global->LDS copies of a T-row tile of width W by NT
+// threads (16-byte chunks; chunk i * NT + 64 wave + lane of the tile for copy i of
+// a lane). LDS chunk (r, pos) receives global chunk (r, pos ^ swz(r)), which is
+// the swizzled layout the reads expect. Rows at or past `rows` re-read row
+// rows - 1: finite values, masked later.
+template <int W, int NT, int T = kT>
 struct TileCopy {
-    static constexpr int CHUNKS = kT * W / 8;
-    static constexpr int N = CHUNKS / kThreads;
-    static_assert(CHUNKS % kThreads == 0, "tile chunks must spread evenly over the workgroup");
-    // Copy i of a lane reads 256 chunks (4096 bytes) past copy i - 1: its row moves
-    // by a multiple of 16 (W = 128) or 32 (W = 64) rows, which leaves swz unchanged.
-    uint32_t off0;  // global byte offset (in the tile) of the lane's first chunk
-    int row0;       // its tile row
+    static constexpr int CHUNKS = T * W / 8;
+    static constexpr int N = CHUNKS / NT;
+    static constexpr int STEP = NT * 8 / W;  // rows from a lane's copy to its next
+    // swz repeats every 16 rows: copies OFFS apart differ by a constant only
+    static constexpr int OFFS = STEP % 16 == 0 || N == 1 ? 1 : 16 / STEP;
+    static_assert(CHUNKS % NT == 0, "tile chunks must spread evenly over the threads");
+    static_assert(OFFS == 1 || 16 % STEP == 0, "copy offsets do not repeat");
+    uint32_t off[OFFS];  // global byte offsets (in the tile) of the lane's first chunks
+    int row0;            // tile row of its first chunk
     __device__ __forceinline__ TileCopy(int wave, int lane) {
         const int ci = wave * 64 + lane;
-        const int r = ci / (W / 8), pos = ci % (W / 8);
-        row0 = r;
-        off0 = (uint32_t)((r * W + ((pos ^ swz<W>(r)) * 8)) * 2);
+        const int pos = ci % (W / 8);
+        row0 = ci / (W / 8);
+#pragma unroll
+        for (int j = 0; j < OFFS; ++j) {
+            const int r = row0 + j * STEP;
+            off[j] = (uint32_t)((r * W + ((pos ^ swz<W>(r)) * 8)) * 2);
+        }
+    }
+    __device__ __forceinline__ uint32_t offset(int i) const {
+        return off[i % OFFS] + (uint32_t)((i - i % OFFS) * NT * 16);
     }
     __device__ __forceinline__ void issue(const uint16_t* g, int first, int rows, uint16_t* tile, int wave) const {
         const char* t = (const char*)(g + (size_t)first * W);
-        if (first + kT <= rows) {  // workgroup-uniform
+        if (first + T <= rows) {  // workgroup-uniform
 #pragma unroll
-            for (int i = 0; i < N; ++i)
-                copy16_to_lds(t, off0 + i * kThreads * 16, tile + (i * kThreads + wave * 64) * 8);
+            for (int i = 0; i < N; ++i) copy16_to_lds(t, offset(i), tile + (i * NT + wave * 64) * 8);
             return;
         }
         const int last = rows - first - 1;
 #pragma unroll
         for (int i = 0; i < N; ++i) {
-            const int r = row0 + i * (kThreads * 8 / W);
-            const uint32_t o = off0 + i * kThreads * 16;
-            copy16_to_lds(t, r > last ? o - (r - last) * W * 2 : o, tile + (i * kThreads + wave * 64) * 8);
+            const int r = row0 + i * STEP;
+            const uint32_t o = offset(i);
+            copy16_to_lds(t, r > last ? o - (r - last) * W * 2 : o, tile + (i * NT + wave * 64) * 8);
+        }
+    }
+};
+
+// Adds up the accumulators of a wave's partners in the other groups of a
+// workgroup: the waves of groups 1, 2, ... leave theirs in LDS as they lie in the
+// lanes (16 bytes per lane, no conflicts), and the wave of group 0 with the same
+// rows adds them in group order. Every wave of the workgroup calls store, passes
+// a barrier, and group 0 calls add.
+template <int BLK>
+struct Partial {
+    float4 x[4 * BLK][64];
+    __device__ __forceinline__ void store(int blk, const f32x16& a, int lane) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) x[4 * blk + j][lane] = make_float4(a[4 * j], a[4 * j + 1], a[4 * j + 2], a[4 * j + 3]);
+    }
+    __device__ __forceinline__ void add(int blk, f32x16& a, int lane) const {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const float4 w = x[4 * blk + j][lane];
+            a[4 * j] += w.x;
+            a[4 * j + 1] += w.y;
+            a[4 * j + 2] += w.z;
+            a[4 * j + 3] += w.w;
         }
     }
 };
@@ -197,30 +231,42 @@ __device__ __forceinline__ void q_dscores(f32x16& s, const f32x16& dp, float c, 
 // ------------------------------------------------------------------ dQ and D
 
 template <int R, int DV>
-struct alignas(16) DqSmem {
+struct alignas(16) DqTiles {
     uint16_t k[2][kT * R];
     uint16_t v[2][kT * DV];
 };
+// GW waves share each tile; KS key groups of GW waves walk the key tiles in turn,
+// each with tiles of its own. After the walk the same LDS holds the partial dQ.
+template <int R, int DV, int GW, int KS>
+union DqSmem {
+    DqTiles<R, DV> tiles[KS];
+    Partial<R / 32> part[(KS - 1) * GW + (KS == 1)];
+};
 
-template <int R, int DV>
-__global__ __launch_bounds__(kThreads, 2) void bwd_dq_kernel(const PrefillBwdParams p, int n_groups) {
+template <int R, int DV, int GW, int KS>
+__global__ __launch_bounds__(64 * GW * KS, KS == 1 ? 2 : 1) void bwd_dq_kernel(const PrefillBwdParams p) {
     constexpr int KSTEPS = R / 16, DSTEPS = DV / 16, RBLK = R / 32;
-    __shared__ DqSmem<R, DV> sm;
+    constexpr int NT = 64 * GW;
+    __shared__ DqSmem<R, DV, GW, KS> smem;
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = threadIdx.x & 63, all_wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = KS == 1 ? all_wave : all_wave % GW;  // wave of its key group
+    const int kgrp = KS == 1 ? 0 : all_wave / GW;
+    DqTiles<R, DV>& sm = smem.tiles[kgrp];
     const int half = lane >> 5, col = lane & 31;
 
-    // workgroup -> (KV sequence, 32 rows x HPW heads), XCD-aware, heaviest first
-    const int HPW = gcd4(p.G);
-    const int RB = 4 / HPW;
+    // workgroup -> (KV sequence, 32 rows x HPW heads): the heaviest block of every
+    // sequence, then the next heaviest, so that the last workgroups to start are
+    // the lightest of all; with a multiple of 8 sequences the round-robin dispatch
+    // keeps each on one XCD
+    const int HPW = heads_per_group(p.G, GW);
+    const int RB = GW / HPW;
     const int BM = 32 * RB;
     const int nqb = (p.Sq + BM - 1) / BM;
-    const int per_xcd = (n_groups + kXcds - 1) / kXcds;
-    const int logical = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
-    if (logical >= n_groups) return;
-    const int pair = logical / nqb, rank = logical % nqb;
-    const int qb = p.causal ? nqb - 1 - rank : rank;
     const int groups_per_kv = p.G / HPW;
+    const int pairs = p.B * p.Hkv * groups_per_kv;
+    const int pair = (int)(blockIdx.x % (unsigned)pairs), rank = (int)(blockIdx.x / (unsigned)pairs);
+    const int qb = p.causal ? nqb - 1 - rank : rank;
     const int b = pair / (p.Hkv * groups_per_kv);
     const int gy = pair % (p.Hkv * groups_per_kv);
     const int g = gy / groups_per_kv;
@@ -239,10 +285,21 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dq_kernel(const PrefillBwdPar
     const uint16_t* kg = (const uint16_t*)p.k + ((size_t)b * p.Hkv + g) * p.Sk * R;
     const uint16_t* vg = (const uint16_t*)p.v + ((size_t)b * p.Hkv + g) * p.Sk * DV;
 
-    const TileCopy<R> kc(wave, lane);
-    const TileCopy<DV> vc(wave, lane);
-    kc.issue(kg, 0, p.Sk, sm.k[0], wave);
-    vc.issue(vg, 0, p.Sk, sm.v[0], wave);
+    int key_end = p.Sk;
+    if (p.causal) {
+        const int last = q0 + BM + off;
+        key_end = last < key_end ? last : key_end;
+    }
+    const int ntiles = (key_end + kT - 1) / kT;
+    // this key group's tiles: kgrp, kgrp + KS, ...; every group passes the same barriers
+    const int nsteps = (ntiles + KS - 1) / KS;
+
+    const TileCopy<R, NT> kc(wave, lane);
+    const TileCopy<DV, NT> vc(wave, lane);
+    if (KS == 1 || kgrp < ntiles) {
+        kc.issue(kg, kgrp * kT, p.Sk, sm.k[0], wave);
+        vc.issue(vg, kgrp * kT, p.Sk, sm.v[0], wave);
+    }
 
     // B operands: Q^T (dims 16m + 8 half .. + 7 of the lane's row) and dO^T; D from dO and O
     bf16x8 qreg[KSTEPS], dreg[DSTEPS];
@@ -259,18 +316,12 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dq_kernel(const PrefillBwdPar
     }
     D = xor32_sum(D);
     const float lse2 = p.lse[rowq * p.Sq + qr] * kLog2e;
-    if (half == 0 && row_ok) {
+    if (half == 0 && row_ok && kgrp == 0) {
         p.delta[rowq * p.Sq + qrow] = D;
         p.lse2[rowq * p.Sq + qrow] = lse2;
     }
     const float c = p.qscale;
 
-    int key_end = p.Sk;
-    if (p.causal) {
-        const int last = q0 + BM + off;
-        key_end = last < key_end ? last : key_end;
-    }
-    const int ntiles = (key_end + kT - 1) / kT;
     const int wave_last_key = p.causal ? qw0 + 31 + off : p.Sk - 1;
     const int lim = p.causal ? (qrow + off < p.Sk - 1 ? qrow + off : p.Sk - 1) : p.Sk - 1;
 
@@ -286,14 +337,16 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dq_kernel(const PrefillBwdPar
     __builtin_amdgcn_s_waitcnt(0x0F70);
     __syncthreads();
 
-    for (int t = 0; t < ntiles; ++t) {
+    for (int t = 0; t < nsteps; ++t) {
         const int cur = t & 1;
-        const int base = t * kT;
-        if (t + 1 < ntiles) {
-            kc.issue(kg, base + kT, p.Sk, sm.k[cur ^ 1], wave);
-            vc.issue(vg, base + kT, p.Sk, sm.v[cur ^ 1], wave);
+        const int tile = t * KS + kgrp;
+        const int base = tile * kT;
+        const bool more = tile + KS < ntiles;
+        if (more) {
+            kc.issue(kg, base + KS * kT, p.Sk, sm.k[cur ^ 1], wave);
+            vc.issue(vg, base + KS * kT, p.Sk, sm.v[cur ^ 1], wave);
         }
-        if (base <= wave_last_key) {
+        if (base <= wave_last_key && (KS == 1 || tile < ntiles)) {
             const uint16_t* ks = sm.k[cur];
             const uint16_t* vs = sm.v[cur];
             const bool needs_mask = (p.causal && base + kT - 1 > qw0 + off) || base + kT > p.Sk;
@@ -327,8 +380,22 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dq_kernel(const PrefillBwdPar
                 }
             }
         }
-        if (t + 1 < ntiles) wait_loads();  // this wave's part of the next tile has landed
+        if (more) wait_loads();  // this wave's part of the next tile has landed
         __syncthreads();
+    }
+
+    // ---- key groups: group 0 adds up the partial dQ (the last barrier has freed the tiles)
+    if constexpr (KS > 1) {
+        if (kgrp > 0) {
+#pragma unroll
+            for (int rb = 0; rb < RBLK; ++rb) smem.part[(kgrp - 1) * GW + wave].store(rb, dq[rb], lane);
+        }
+        __syncthreads();
+        if (kgrp > 0) return;
+#pragma unroll 1
+        for (int k = 1; k < KS; ++k)
+#pragma unroll
+            for (int rb = 0; rb < RBLK; ++rb) smem.part[(k - 1) * GW + wave].add(rb, dq[rb], lane);
     }
 
     // dQ rows: lane (half, col) holds dims 32 rb + 8 (v/4) + 4 half + v % 4 of row qrow
@@ -348,27 +415,35 @@ __global__ __launch_bounds__(kThreads, 2) void bwd_dq_kernel(const PrefillBwdPar
 
 // ------------------------------------------------------------------ dK and dV
 
-template <int R, int DV>
-struct alignas(16) KvSmem {
-    uint16_t q[2][kT * R];
-    uint16_t d[2][kT * DV];
-    float lse2[2][kT];  // log2-domain log-sum-exp of the tile's rows
-    float dl[2][kT];    // D of the tile's rows
+template <int R, int DV, int T>
+struct alignas(16) KvTiles {
+    uint16_t q[2][T * R];
+    uint16_t d[2][T * DV];
+    float lse2[2][T];  // log2-domain log-sum-exp of the tile's rows
+    float dl[2][T];    // D of the tile's rows
+};
+// KW waves of 32 keys share each query tile; QG query groups of KW waves walk the
+// query tiles in turn, each with tiles of its own. After the walk the same LDS
+// holds the partial dK and dV.
+template <int R, int DV, int KW, int QG, int T>
+union KvSmem {
+    KvTiles<R, DV, T> tiles[QG];
+    Partial<(R + DV) / 32> part[(QG - 1) * KW + (QG == 1)];
 };
 
 // Issue the copies of query tile `it` (head g G + it % G, rows from
-// (t0 + n_rt - 1 - it / G) 64) into buffer `buf`: Q and dO rows by all waves, the rows'
+// (t0 + n_rt - 1 - it / G) T) into buffer `buf`: Q and dO rows by all waves, the rows'
 // lse2 by wave 0 and D by wave 1 (one float per lane, rows clamped to Sq - 1).
-template <int R, int DV>
-__device__ __forceinline__ void issue_qtile(const PrefillBwdParams& p, KvSmem<R, DV>& sm, const TileCopy<R>& qc,
-                                            const TileCopy<DV>& dc, int it, int buf, int b, int g, int t0,
-                                            int n_rt, int wave, int lane) {
+template <int R, int DV, int NT, int T>
+__device__ __forceinline__ void issue_qtile(const PrefillBwdParams& p, KvTiles<R, DV, T>& sm,
+                                            const TileCopy<R, NT, T>& qc, const TileCopy<DV, NT, T>& dc, int it,
+                                            int buf, int b, int g, int t0, int n_rt, int wave, int lane) {
     const int hh = g * p.G + it % p.G;
-    const int row0 = (t0 + n_rt - 1 - it / p.G) * kT;
+    const int row0 = (t0 + n_rt - 1 - it / p.G) * T;
     const size_t rowq = (size_t)b * p.Hq + hh;
     qc.issue((const uint16_t*)p.q + rowq * p.Sq * R, row0, p.Sq, sm.q[buf], wave);
     dc.issue((const uint16_t*)p.dout + rowq * p.Sq * DV, row0, p.Sq, sm.d[buf], wave);
-    if (wave < 2) {
+    if (wave < 2 && (T == 64 || lane < T)) {
         int r = row0 + lane;
         r = r < p.Sq ? r : p.Sq - 1;
         const float* src = wave == 0 ? p.lse2 : p.delta;
@@ -376,24 +451,48 @@ __device__ __forceinline__ void issue_qtile(const PrefillBwdParams& p, KvSmem<R,
     }
 }
 
-// Register budget: the dK and dV accumulators (r + d_v per lane) and the K and V
-// rows fit two workgroups per CU while r + d_v < 192.
-template <int R, int DV>
-__global__ __launch_bounds__(kThreads, R + DV >= 192 ? 1 : 2) void bwd_dkdv_kernel(const PrefillBwdParams p,
-                                                                                    int n_groups) {
-    constexpr int KSTEPS = R / 16, DSTEPS = DV / 16, RBLK = R / 32, DBLK = DV / 32;
-    constexpr int KB = 4 * 32;  // keys per workgroup
-    __shared__ KvSmem<R, DV> sm;
+// Order of the dK/dV workgroups. Longest first over all sequences balances the
+// CUs: with the workgroups of one sequence after the other, a CU's two resident
+// workgroups were both of the longest or both of the shortest (606 against 522 us
+// at 2 x 4096 tokens, 954 against 723 us at 4 x 4096; r 32, d_v 128, 32 query
+// heads over 8). Where the key blocks of one sequence fill an XCD by themselves
+// (64 slots) and read the same G heads' tiles, keeping to one sequence at a time
+// serves those reads from its L2: 2.84 against 2.95 ms at 4 x 8192. With r + d_v of
+// 192 or more (one workgroup per CU, more work per byte) the balance counts more
+// (5.50 against 5.73 ms there at r 128), and with G = 1 as well (1.40 against
+// 1.42 ms at 2 x 8192, 32 heads).
+__host__ __device__ constexpr bool bwd_by_sequence(int R, int DV, int G, int nkb, int KW) {
+    return R + DV < 192 && KW == 4 && G >= 4 && nkb >= 64;
+}
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+// Register budget: the dK and dV accumulators (r + d_v per lane) and the K and V
+// rows fit two waves per SIMD while r + d_v < 192.
+template <int R, int DV, int KW, int QG, int T>
+__global__ __launch_bounds__(64 * KW * QG, R + DV >= 192 || KW * QG > 4 ? 1 : 2) void bwd_dkdv_kernel(
+    const PrefillBwdParams p) {
+    constexpr int KSTEPS = R / 16, DSTEPS = DV / 16, RBLK = R / 32, DBLK = DV / 32;
+    constexpr int KB = KW * 32;  // keys per workgroup
+    constexpr int NT = 64 * KW;
+    __shared__ KvSmem<R, DV, KW, QG, T> smem;
+
+    const int lane = threadIdx.x & 63, all_wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = QG == 1 ? all_wave : all_wave % KW;  // wave of its query group
+    const int qgrp = QG == 1 ? 0 : all_wave / KW;
+    KvTiles<R, DV, T>& sm = smem.tiles[qgrp];
     const int half = lane >> 5, col = lane & 31;
 
-    // workgroup -> (KV sequence, 128 keys), XCD-aware, longest query range first
+    // workgroup -> (KV sequence, KB keys), longest query range first: over all
+    // sequences as in the dQ kernel, or sequence by sequence (bwd_by_sequence)
     const int nkb = (p.Sk + KB - 1) / KB;
-    const int per_xcd = (n_groups + kXcds - 1) / kXcds;
-    const int logical = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
-    if (logical >= n_groups) return;
-    const int pair = logical / nkb, kbi = logical % nkb;
+    const int pairs = p.B * p.Hkv;
+    int pair = (int)(blockIdx.x % (unsigned)pairs), kbi = (int)(blockIdx.x / (unsigned)pairs);
+    if (bwd_by_sequence(R, DV, p.G, nkb, KW)) {
+        const int n = pairs * nkb, per_xcd = (n + kXcds - 1) / kXcds;
+        const int logical = (int)(blockIdx.x % kXcds) * per_xcd + (int)(blockIdx.x / kXcds);
+        if (logical >= n) return;
+        pair = logical / nkb;
+        kbi = logical % nkb;
+    }
     const int b = pair / p.Hkv, g = pair % p.Hkv;
     const int k0g = kbi * KB;              // first key of the workgroup
     const int k0 = k0g + wave * 32;        // first key of the wave
@@ -411,14 +510,16 @@ __global__ __launch_bounds__(kThreads, R + DV >= 192 ? 1 : 2) void bwd_dkdv_kern
     // query tiles that see any key of the workgroup
     int first_row = p.causal ? k0g - off : 0;
     first_row = first_row < 0 ? 0 : first_row;
-    const int t0 = first_row / kT;
-    const int nt = (p.Sq + kT - 1) / kT;
+    const int t0 = first_row / T;
+    const int nt = (p.Sq + T - 1) / T;
     const int n_rt = nt - t0;
     const int n_iter = n_rt * p.G;  // (tile, head) pairs, tiles descending, heads innermost
+    // this query group's pairs: qgrp, qgrp + QG, ...; every group passes the same barriers
+    const int nsteps = (n_iter + QG - 1) / QG;
 
-    const TileCopy<R> qc(wave, lane);
-    const TileCopy<DV> dc(wave, lane);
-    if (n_iter > 0) issue_qtile<R, DV>(p, sm, qc, dc, 0, 0, b, g, t0, n_rt, wave, lane);
+    const TileCopy<R, NT, T> qc(wave, lane);
+    const TileCopy<DV, NT, T> dc(wave, lane);
+    if (qgrp < n_iter) issue_qtile<R, DV, NT, T>(p, sm, qc, dc, qgrp, 0, b, g, t0, n_rt, wave, lane);
 
     // B operands of S = Q K^T and dP = dO V^T: the lane's key row
     bf16x8 kreg[KSTEPS], vreg[DSTEPS];
@@ -448,16 +549,18 @@ __global__ __launch_bounds__(kThreads, R + DV >= 192 ? 1 : 2) void bwd_dkdv_kern
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt 0, known to the compiler
     __syncthreads();
 
-    for (int it = 0; it < n_iter; ++it) {
-        const int cur = it & 1;
-        const int i0 = (t0 + n_rt - 1 - it / p.G) * kT;  // first query row of the tile
-        if (it + 1 < n_iter) issue_qtile<R, DV>(p, sm, qc, dc, it + 1, cur ^ 1, b, g, t0, n_rt, wave, lane);
-        if (!(p.causal && i0 + kT - 1 + off < k0)) {  // some row of the tile sees the wave's keys
+    for (int step = 0; step < nsteps; ++step) {
+        const int cur = step & 1;
+        const int it = step * QG + qgrp;
+        const int i0 = (t0 + n_rt - 1 - it / p.G) * T;  // first query row of the tile
+        const bool more = it + QG < n_iter;
+        if (more) issue_qtile<R, DV, NT, T>(p, sm, qc, dc, it + QG, cur ^ 1, b, g, t0, n_rt, wave, lane);
+        if ((QG == 1 || it < n_iter) && !(p.causal && i0 + T - 1 + off < k0)) {  // some row of the tile sees the wave's keys
             const uint16_t* qs = sm.q[cur];
             const uint16_t* ds = sm.d[cur];
-            const bool needs_mask = (p.causal && i0 + off < k0 + 31) || i0 + kT > p.Sq || k0 + 32 > p.Sk;
+            const bool needs_mask = (p.causal && i0 + off < k0 + 31) || i0 + T > p.Sq || k0 + 32 > p.Sk;
 #pragma unroll
-            for (int qb = 0; qb < 2; ++qb) {
+            for (int qb = 0; qb < T / 32; ++qb) {
                 // S and dP of query rows i0 + 32 qb + (8 (v/4) + 4 half + v % 4), key col
                 f32x16 s, dp;
 #pragma unroll
@@ -494,8 +597,29 @@ __global__ __launch_bounds__(kThreads, R + DV >= 192 ? 1 : 2) void bwd_dkdv_kern
                 }
             }
         }
-        if (it + 1 < n_iter) wait_loads();  // this wave's part of the next tile has landed
+        if (more) wait_loads();  // this wave's part of the next tile has landed
         __syncthreads();
+    }
+
+    // ---- query groups: group 0 adds up the partial dK and dV
+    if constexpr (QG > 1) {
+        if (qgrp > 0) {
+            auto& w = smem.part[(qgrp - 1) * KW + wave];
+#pragma unroll
+            for (int d = 0; d < DBLK; ++d) w.store(d, dva[d], lane);
+#pragma unroll
+            for (int rb = 0; rb < RBLK; ++rb) w.store(DBLK + rb, dka[rb], lane);
+        }
+        __syncthreads();
+        if (qgrp > 0) return;
+#pragma unroll 1
+        for (int k = 1; k < QG; ++k) {
+            const auto& w = smem.part[(k - 1) * KW + wave];
+#pragma unroll
+            for (int d = 0; d < DBLK; ++d) w.add(d, dva[d], lane);
+#pragma unroll
+            for (int rb = 0; rb < RBLK; ++rb) w.add(DBLK + rb, dka[rb], lane);
+        }
     }
 
     // dK, dV rows: lane (half, col) holds keys k0 + 8 (v/4) + 4 half + v % 4, column col of each block
@@ -516,26 +640,82 @@ __global__ __launch_bounds__(kThreads, R + DV >= 192 ? 1 : 2) void bwd_dkdv_kern
 
 // ------------------------------------------------------------------ dispatch
 
+template <int R, int DV, int GW, int KS>
+static hipError_t run_dq(const PrefillBwdParams& p, hipStream_t st) {
+    const int HPW = heads_per_group(p.G, GW);
+    const int BM = 32 * (GW / HPW);
+    const long groups = (long)((p.Sq + BM - 1) / BM) * p.Hkv * (p.G / HPW) * p.B;
+    if (groups * 64 * GW * KS > 0xffffffffL) return hipErrorInvalidValue;
+    if (groups == 0) return hipSuccess;
+    hipLaunchKernelGGL((bwd_dq_kernel<R, DV, GW, KS>), dim3((unsigned)groups), dim3(64 * GW * KS), 0, st, p);
+    return hipGetLastError();
+}
+
+template <int R, int DV, int KW, int QG, int T>
+static hipError_t run_dkdv(const PrefillBwdParams& p, hipStream_t st) {
+    const long nkb = (p.Sk + 32 * KW - 1) / (32 * KW);
+    long groups = nkb * p.Hkv * p.B;
+    if (bwd_by_sequence(R, DV, p.G, (int)nkb, KW)) groups = (groups + kXcds - 1) / kXcds * kXcds;
+    if (groups * 64 * KW * QG > 0xffffffffL) return hipErrorInvalidValue;
+    if (groups == 0) return hipSuccess;
+    hipLaunchKernelGGL((bwd_dkdv_kernel<R, DV, KW, QG, T>), dim3((unsigned)groups), dim3(64 * KW * QG), 0, st, p);
+    return hipGetLastError();
+}
+
+// Workgroup shapes. A unit is one wave's block of 32 query rows of one head (dQ)
+// or of 32 keys of one KV head (dK/dV). As in the forward, a call of few units
+// leaves CUs idle, or all its workgroups resident at once so that the longest walk
+// sets its time: fewer units per workgroup and several groups that walk the tiles
+// in turn shorten it. us per call, four units x 1 group against the adopted shape,
+// r 32, 32 query heads over 8, d_v 128, unless stated:
+//   dQ, up to 1024 units (d_v 64: 1536), two units x 2 key groups: 512 tokens
+//     14.9 / 10.8, 1024 tokens 24.9 / 18.2; r 128, 1024 tokens 39.0 / 30.8; 12
+//     heads, d_v 64, 2 x 2048 tokens 36.5 / 24.7
+//   dQ, up to 2048 units and 20 tiles or more, four units x 2: 2048 tokens 48.4 / 40.4
+//   dK/dV, r + d_v < 192 (two waves per SIMD): up to 1024 units (d_v 64: 768, walks
+//     of 16 tiles or more) two units x 4 query groups on 32-row tiles, which fit
+//     them in the LDS: 1024 tokens 129 / 54, 2048 tokens 253 / 100; up to 3072 units
+//     two units x 2, 32-row tiles (two workgroups per CU): 2 x 4096 tokens 520 / 394,
+//     10 x 952 142 / 122; for d_v 64 up to 1536 units two units x 2, 64-row tiles:
+//     12 heads, 4096 tokens 92.8 / 57.8
+//   dK/dV, r + d_v >= 192 (one wave per SIMD): up to 1024 units two units x 2,
+//     64-row tiles: r 128, 2048 tokens 339 / 192
+// On the other side of the lines, four units x 1 is faster: dQ 3 x 500 tokens, 32
+// KV heads, 16.4 against 19.2 with two units x 2; dK/dV 4 x 4096 tokens 727 against
+// 757, r 128, 32 KV heads, 2048 tokens 104 against 123; 12 heads, d_v 64, 8 x 1000
+// tokens 37 against 40.
+template <int R, int DV>
+static hipError_t dq(const PrefillBwdParams& p, hipStream_t st) {
+    const long units = (long)p.B * p.Hq * ((p.Sq + 31) / 32);
+    const long tiles = ((long)p.Sk + kT - 1) / kT;
+    if (tiles >= 2 && units <= (R + DV <= 128 ? 1536 : 1024)) return run_dq<R, DV, 2, 2>(p, st);
+    if (tiles >= 20 && units <= 2048) return run_dq<R, DV, 4, 2>(p, st);
+    return run_dq<R, DV, 4, 1>(p, st);
+}
+
+template <int R, int DV>
+static hipError_t dkdv(const PrefillBwdParams& p, hipStream_t st) {
+    const long units = (long)p.B * p.Hkv * ((p.Sk + 31) / 32);
+    const long walk = ((long)p.Sq + kT - 1) / kT * p.G;  // 64-row query tiles of the longest walk
+    if (walk >= 2) {
+        if constexpr (R + DV >= 192) {
+            if (units <= 1024) return run_dkdv<R, DV, 2, 2, 64>(p, st);
+        } else {
+            if (units <= (DV == 64 ? 768 : 1024) && (DV != 64 || walk >= 16)) return run_dkdv<R, DV, 2, 4, 32>(p, st);
+            if constexpr (DV == 64) {
+                if (units <= 1536) return run_dkdv<R, DV, 2, 2, 64>(p, st);
+            } else {
+                if (units <= 3072) return run_dkdv<R, DV, 2, 2, 32>(p, st);
+            }
+        }
+    }
+    return run_dkdv<R, DV, 4, 1, 64>(p, st);
+}
+
 template <int R, int DV>
 static hipError_t run(const PrefillBwdParams& p, hipStream_t st) {
-    const int HPW = gcd4(p.G);
-    const int BM = 32 * (4 / HPW);
-    const long nqb = (p.Sq + BM - 1) / BM;
-    const long groups_q = nqb * p.Hkv * (p.G / HPW) * p.B;
-    const long nkb = (p.Sk + 127) / 128;
-    const long groups_k = nkb * p.Hkv * p.B;
-    const long lq = (groups_q + kXcds - 1) / kXcds * kXcds, lk = (groups_k + kXcds - 1) / kXcds * kXcds;
-    if (lq * kThreads > 0xffffffffL || lk * kThreads > 0xffffffffL) return hipErrorInvalidValue;
-    if (lq > 0) {
-        hipLaunchKernelGGL((bwd_dq_kernel<R, DV>), dim3((unsigned)lq), dim3(kThreads), 0, st, p, (int)groups_q);
-        const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    if (lk > 0) {
-        hipLaunchKernelGGL((bwd_dkdv_kernel<R, DV>), dim3((unsigned)lk), dim3(kThreads), 0, st, p, (int)groups_k);
-        return hipGetLastError();
-    }
-    return hipSuccess;
+    const hipError_t e = dq<R, DV>(p, st);
+    return e == hipSuccess ? dkdv<R, DV>(p, st) : e;
 }
 
 template <int R>

@@ -98,6 +98,28 @@ def test_backward_shapes_and_masks(shape):
     isolated(spec, structured=True)
 
 
+@pytest.mark.parametrize("r,dv,shape", [
+    (r, dv, shape) for r, dv in ((32, 64), (32, 128), (64, 64), (64, 128), (128, 128)) for shape in (
+        (1, 4, 1, 300, 300, True),    # two units per workgroup in groups, walks over 4 heads
+        (2, 6, 2, 257, 270, False),   # G = 3, ragged keys, no mask
+        (6, 48, 48, 100, 100, True),  # 1152 units: dQ by four; dK/dV by two on 32-row tiles, or by four
+        (12, 72, 72, 97, 100, True),  # 3456 units: four per workgroup everywhere
+    )] + [
+    (32, 128, (1, 32, 8, 1050, 1250, True)),  # dQ in four units x 2 key groups
+    (64, 64, (1, 48, 8, 1050, 1290, True)),
+], ids=lambda x: "x".join(map(str, x)) if isinstance(x, tuple) else str(x))
+def test_backward_workgroup_shapes(r, dv, shape):
+    """The workgroup shapes of both kernels (units per workgroup x groups), every gradient.
+
+    Peaked rows up to r 64. At r 128 the planted logit (22) leaves dS = P (dP - D) as the difference
+    of nearly equal sums: their fp32 rounding, 2^-24 (|dO||V| + |dO||O|) per score carried through
+    dK = scale dS^T Q, is up to 0.31 of ||dK|| (fp64, 2 x 6 heads, 257 x 270, no mask), far over the
+    bar, against 1e-5 of it for i.i.d. inputs, which those shapes take."""
+    B, Hq, Hkv, Sq, Sk, causal = shape
+    isolated(with_shape(BASE, config_id=1050 + r, batch=B, h_q=Hq, h_kv=Hkv, seq_q=Sq, seq_k=Sk, causal=causal, r=r,
+                        d_v=dv), structured=r < 128)
+
+
 def forward_lse(q, k, v, spec, dev):
     from paper_2603_04427_amd import tk_attn_prefill_lse
     return tk_attn_prefill_lse(q.to(dev), k.to(dev), v.to(dev), causal=spec.causal, scale=spec.softmax_scale)
