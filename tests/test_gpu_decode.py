@@ -211,3 +211,25 @@ def test_bad_block_table_entry_gives_nan_for_that_sequence():
     out = decode_on_gpu(d2, spec, dev)
     assert torch.isnan(out[1].float()).all()
     assert torch.equal(out[0], good[0]) and torch.equal(out[2], good[2])
+
+
+@pytest.mark.parametrize("paged,kdt", [(False, "bf16"), (True, "fp8")])
+@pytest.mark.parametrize("B,h_kv,ctx,lens", [
+    (16, 8, 2049, [2049, 257] + [0, 1, 128, 129, 700, 2048] * 2 + [1, 1]),  # two splits a sequence, one owed most
+    (8, 8, 4096, [4096, 3000, 17, 4096, 1, 512, 513, 2047]),                # four
+    (2, 2, 40000, [40000, 1]),                                              # 64: all but one go to the first
+    (5, 3, 20000, [1, 1, 1, 1, 20000]),
+    (64, 2, 3000, [3000] * 3 + list(range(0, 61 * 40, 40))),                # a sequence in every lane
+    (65, 2, 1500, [1500] + list(range(1, 65))),                             # more sequences than lanes: not dealt
+    (4, 8, 8192, [5000, 5000, 5000, 5001]),                                 # nearly equal
+])
+def test_splits_dealt_by_length(B, h_kv, ctx, lens, paged, kdt):
+    """Split contexts of sequences of unequal lengths, whose splits are dealt by length:
+    every output against the oracle, and the same bits from a second call."""
+    dev = device()
+    spec = with_shape(BASE, config_id=600 + B, batch=B, h_q=4 * h_kv, h_kv=h_kv, ctx=ctx, ctx_lens=tuple(lens),
+                      k_dtype=kdt, paged=paged, block_size=64)
+    out, ref = run_case(spec, structured=True)
+    gate(out, ref, kdt, f"dealt {spec}")
+    d = make_decode(spec, structured=True)
+    assert torch.equal(decode_on_gpu(d, spec, dev), out)
