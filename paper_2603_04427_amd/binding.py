@@ -1,14 +1,23 @@
-"""ctypes binding of libtkattn.so, with the C entry points' names.
+"""Binding of libtkattn.so, with the C entry points' names.
 
 Argument marshalling only: shapes are read from the tensors, checked for
 consistency, and passed with the tensors' device pointers and torch's current
 HIP stream to the C ABI declared in include/tk_attn.h. Every step of the
 computation runs in the HIP kernels; there is no other code path. If the
 library has not been built, the first call raises instead of falling back.
+
+The plain calls first go to _tkcall (csrc/torch_call.cpp), which does the same
+marshalling in C++ for plain tensors on the current stream and declines the rest;
+what it declines is marshalled here, through ctypes, and raises here if it is
+wrong. A prepared call is bound there once and then launches without conversions.
+Small calls were bound by this module's host work: a projection of 3 tokens took
+11 us a call, an append of 2 rows 13, a 32-token prefill 12.4 (kernels of 2 to 5).
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 from typing import Optional
 
@@ -38,7 +47,14 @@ SIGNATURES = {
     "tk_version": ([], _i),
 }
 
+# the entry points that _tkcall calls, in the order of its connect()
+_CONNECTED = ("tk_attn_prefill", "tk_attn_prefill_lse", "tk_attn_prefill_backward",
+              "tk_attn_prefill_backward_workspace_bytes", "tk_attn_decode", "tk_attn_decode_noalloc",
+              "tk_cache_append", "tk_project_heads")
+_CALL_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_tkcall.so")
+
 _lib = None
+_call = None
 
 
 class TkError(RuntimeError):
@@ -61,6 +77,31 @@ def lib() -> ctypes.CDLL:
             fn.restype = res
         _lib = L
     return _lib
+
+
+def _load_call():
+    """The _tkcall module, connected to the loaded library (raises if either has not been built)."""
+    global _call
+    if _call is None:
+        L = lib()
+        if not os.path.exists(_CALL_PATH):
+            raise RuntimeError(f"_tkcall.so not found at {_CALL_PATH}; build it with "
+                               "`python -m paper_2603_04427_amd.build`")
+        loader = importlib.machinery.ExtensionFileLoader("_tkcall", _CALL_PATH)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_loader("_tkcall", loader))
+        loader.exec_module(module)
+        module.connect(*(ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in _CONNECTED))
+        _call = module
+    return _call
+
+
+def _native(name: str, *args):
+    """The plain call through _tkcall: its result, or None if it is left to this module."""
+    out = getattr(_call or _load_call(), name)(*args)
+    if type(out) is int:
+        raise TkError(out, "tk_cache_append" if name == "cache_append" else
+                      "tk_project_heads" if name == "project_heads" else "tk_attn_" + name)
+    return out
 
 
 def tk_status_str(status: int) -> str:
@@ -104,9 +145,13 @@ class PreparedCall:
         self.args = args
         self.keep = keep  # tensors whose memory the pointers refer to
         self.result = keep[-1] if result is None else result
+        self._bound = self._bound_args = None
 
     def __call__(self):
-        st = self.fn(*self.args)
+        if self._bound_args is not self.args:
+            self._bound = (_call or _load_call()).bind(self.name, self.args)
+            self._bound_args = self.args
+        st = self._bound()
         if st != TK_OK:
             raise TkError(st, self.name)
         return self.result
@@ -135,7 +180,8 @@ def prepare_prefill(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor, O: Option
 def tk_attn_prefill(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor, O: Optional[torch.Tensor] = None,
                     causal: bool = True, scale: float = 0.0, stream=None) -> torch.Tensor:
     """O = softmax(scale Q K^T [causal]) V for Q [B,Hq,Sq,r], K [B,Hkv,Sk,r], V [B,Hkv,Sk,dv]."""
-    return prepare_prefill(Q, K, V, O, causal, scale, stream)()
+    out = _native("prefill", Q, K, V, O, causal, scale, stream)
+    return prepare_prefill(Q, K, V, O, causal, scale, stream)() if out is None else out
 
 
 def _prefill_shapes(Q, K, V):
@@ -170,7 +216,8 @@ def tk_attn_prefill_lse(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor, O: Op
                         lse: Optional[torch.Tensor] = None, causal: bool = True, scale: float = 0.0,
                         stream=None):
     """bf16 prefill that also returns each row's log-sum-exp (fp32 [B, Hq, Sq]): (O, lse)."""
-    return prepare_prefill_lse(Q, K, V, O, lse, causal, scale, stream)()
+    out = _native("prefill_lse", Q, K, V, O, lse, causal, scale, stream)
+    return prepare_prefill_lse(Q, K, V, O, lse, causal, scale, stream)() if out is None else out
 
 
 def tk_attn_prefill_backward_workspace_bytes(batch: int, H_q: int, seq_q: int) -> int:
@@ -212,7 +259,10 @@ def tk_attn_prefill_backward(Q: torch.Tensor, K: torch.Tensor, V: torch.Tensor, 
                              dV: Optional[torch.Tensor] = None, workspace: Optional[torch.Tensor] = None,
                              stream=None):
     """Gradients (dQ, dK, dV) of the bf16 prefill given O, dO and the forward's lse."""
-    return prepare_prefill_backward(Q, K, V, O, dO, lse, causal, scale, dQ, dK, dV, workspace, stream)()
+    out = _native("prefill_backward", Q, K, V, O, dO, lse, causal, scale, dQ, dK, dV, workspace, stream)
+    if out is None:
+        out = prepare_prefill_backward(Q, K, V, O, dO, lse, causal, scale, dQ, dK, dV, workspace, stream)()
+    return out
 
 
 def tk_attn_decode_workspace_bytes(batch: int, H_q: int, H_kv: int, max_ctx: int, d_v: int) -> int:
@@ -369,7 +419,8 @@ def tk_cache_append(K_new: torch.Tensor, V_new: torch.Tensor, positions: torch.T
                     V_cache: torch.Tensor, k_scale: Optional[torch.Tensor] = None,
                     block_table: Optional[torch.Tensor] = None, block_size: int = 0, stream=None) -> None:
     """Write T new tokens per sequence into the cache at positions[b] + t (see include/tk_attn.h)."""
-    prepare_cache_append(K_new, V_new, positions, K_cache, V_cache, k_scale, block_table, block_size, stream)()
+    if _native("cache_append", K_new, V_new, positions, K_cache, V_cache, k_scale, block_table, block_size, stream) is None:
+        prepare_cache_append(K_new, V_new, positions, K_cache, V_cache, k_scale, block_table, block_size, stream)()
 
 
 def prepare_project_heads(X: torch.Tensor, Wt: torch.Tensor, n_heads: int, Y: Optional[torch.Tensor] = None,
@@ -396,4 +447,5 @@ def prepare_project_heads(X: torch.Tensor, Wt: torch.Tensor, n_heads: int, Y: Op
 def tk_project_heads(X: torch.Tensor, Wt: torch.Tensor, n_heads: int, Y: Optional[torch.Tensor] = None,
                      stream=None) -> torch.Tensor:
     """Y[b, h, s, :] = X[b, s, :] @ Wt[h * width:(h + 1) * width, :].T, head-major bf16."""
-    return prepare_project_heads(X, Wt, n_heads, Y, stream)()
+    out = _native("project_heads", X, Wt, n_heads, Y, stream)
+    return prepare_project_heads(X, Wt, n_heads, Y, stream)() if out is None else out

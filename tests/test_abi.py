@@ -262,3 +262,20 @@ def test_stream_probe_library_loads_and_rejects_bad_arguments():
     assert f(P_ODD, 4096, P, 256, 0, None) == 1       # misaligned
     assert f(P, 4096, P, 0, 1, None) == 1             # empty grid
     assert f(P, 0, P, 256, 1, None) == 1              # nothing to read
+
+
+def test_bound_calls_convert_arguments_as_ctypes_does():
+    """A bound call (the prepared calls' launch) gives the status that the same
+    arguments give through ctypes; a wrong argument list is an error when bound."""
+    call = tb._load_call()
+    good = (P, P, P, 2, 8, 64, 2, 32, None)
+    for i, bad in ((0, None), (0, ctypes.c_void_p(None)), (1, P_ODD), (3, -1), (3, 2**32 - 1), (5, 65), (7, 6)):
+        args = good[:i] + (bad,) + good[i + 1:]
+        assert call.bind("tk_project_heads", args)() == tb.lib().tk_project_heads(*args) != tb.TK_OK
+    assert call.bind("tk_project_heads", good[:3] + (0,) + good[4:])() == tb.TK_OK  # no rows: nothing to launch
+    with pytest.raises(TypeError):
+        call.bind("tk_project_heads", good[:-1])
+    with pytest.raises(AttributeError):
+        call.bind("tk_project_heads", good[:3] + ("2",) + good[4:])
+    with pytest.raises(ValueError):
+        call.bind("tk_version", ())
