@@ -66,33 +66,17 @@ __device__ __forceinline__ void wait_copies(bool next_in_flight) {
 // between the two waves of each SIMD; the smaller ones run 32x32x16 products,
 // each wave reading the next 16-wide k-step's operands during the current one's
 // products.
-//
-// With KG > 1, KG groups of those waves take the k-tiles of one output tile in
-// turn (group g the k-tiles g, g + KG, ...), each through a ring of its own, and
-// group 0 adds up the partial tiles in LDS in group order: for calls whose tiles
-// are too few to fill the CUs with waves.
-template <int BN, int KG>
-constexpr int proj_threads() { return 64 * (BN / 64) * 2 * KG; }
+template <int BN>
+constexpr int proj_threads() { return 64 * (BN / 64) * 2; }
 
-template <int BN, int BM, int KG>
-union ProjSmem {
-    ProjTile<BN, BM> tile[KG];
-    float4 part[KG - 1 + (KG == 1)][ProjTile<BN, BM>::kWaves][KG == 1 ? 1 : 8 * (BM / 64)][64];  // accumulators as they lie
-};
-
-template <int BN, int BM, int KG>
-__global__ __launch_bounds__((proj_threads<BN, KG>()), 1) void project_kernel(const ProjectParams p) {
+template <int BN, int BM>
+__global__ __launch_bounds__(proj_threads<BN>(), 1) void project_kernel(const ProjectParams p) {
     using T = ProjTile<BN, BM>;
     constexpr int kPThreads = T::kThreads, kWCopies = T::kWCopies, kXCopies = T::kXCopies;
     constexpr int kPBN = BN, kPBM = BM;
-    static_assert(KG == 1 || BM < 256, "the ping-pong tiles take all k-tiles");
-    __shared__ ProjSmem<BN, BM, KG> smem;
-    const int lane = threadIdx.x & 63;
-    const int all_wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wave = KG == 1 ? all_wave : all_wave % T::kWaves;  // wave of its k group
-    const int kgrp = KG == 1 ? 0 : all_wave / T::kWaves;
-    const int tid = wave * 64 + lane;
-    T& sm = smem.tile[kgrp];
+    __shared__ T sm;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wn = wave >> 1, wm = wave & 1;  // (BN / 64) x 2 waves over the tile's columns x tokens
     // XCD-aware order: workgroups are dealt to the 8 XCDs round-robin; each XCD
     // takes a contiguous range of tiles, column tiles fastest, so the column
@@ -222,8 +206,6 @@ __global__ __launch_bounds__((proj_threads<BN, KG>()), 1) void project_kernel(co
                 for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
         const int nk = p.K / kPBK;
-        const int nsteps = (nk + KG - 1) / KG;  // every group passes the same barriers; only its last step can be missing
-        auto has = [&](int t) { return t * KG + kgrp < nk; };
         // operand reads of k-step ks of the k-tile in `st`, and the products of one k-step
         auto read_ops = [&](int st, int ks, bf16x8 (&a)[2], bf16x8 (&b)[T::kMB]) {
             const uint16_t* ws = sm.w[st];
@@ -241,9 +223,9 @@ __global__ __launch_bounds__((proj_threads<BN, KG>()), 1) void project_kernel(co
                 for (int j = 0; j < T::kMB; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
         };
-        if (has(0)) issue(kgrp, 0);
-        if (has(1)) issue(KG + kgrp, 1);
-        wait_copies<T::kCopies>(has(1));  // this lane's copies of k-tile 0 have landed
+        issue(0, 0);
+        if (nk > 1) issue(1, 1);
+        wait_copies<T::kCopies>(nk > 1);  // this lane's copies of k-tile 0 have landed
         __syncthreads();      // ... and everyone's
         static_assert(kPBK == 32, "the pipeline below takes two 16-wide k-steps per k-tile");
         // Software pipeline over the k-steps: the operands of the next k-step are
@@ -253,11 +235,11 @@ __global__ __launch_bounds__((proj_threads<BN, KG>()), 1) void project_kernel(co
         bf16x8 a0[2], b0[T::kMB], a1[2], b1[T::kMB];
         read_ops(0, 0, a0, b0);
         int stage = 0;
-        for (int kt = 0; kt + 1 < nsteps; ++kt) {
+        for (int kt = 0; kt + 1 < nk; ++kt) {
             // the stage k-tile kt + 2 goes to was last read before the barrier that
             // ended iteration kt - 1
-            const bool ahead = has(kt + 2);
-            if (ahead) issue((kt + 2) * KG + kgrp, stage == 0 ? 2 : stage - 1);
+            const bool ahead = kt + 2 < nk;
+            if (ahead) issue(kt + 2, stage == 0 ? 2 : stage - 1);
             read_ops(stage, 1, a1, b1);
             products(a0, b0);
             const int next = stage == kStages - 1 ? 0 : stage + 1;
@@ -268,42 +250,9 @@ __global__ __launch_bounds__((proj_threads<BN, KG>()), 1) void project_kernel(co
             stage = next;
         }
         // the last k-tile
-        if (KG == 1 || has(nsteps - 1)) {
-            read_ops(stage, 1, a1, b1);
-            products(a0, b0);
-            products(a1, b1);
-        }
-
-        // ---- k groups: group 0 adds up the partial tiles
-        if constexpr (KG > 1) {
-            __syncthreads();  // every ring is drained
-            if (kgrp > 0) {
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int j = 0; j < T::kMB; ++j)
-#pragma unroll
-                        for (int g = 0; g < 4; ++g)
-                            smem.part[kgrp - 1][wave][(i * T::kMB + j) * 4 + g][lane] =
-                                make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
-            }
-            __syncthreads();
-            if (kgrp > 0) return;
-#pragma unroll 1
-            for (int k = 1; k < KG; ++k)
-#pragma unroll
-                for (int i = 0; i < 2; ++i)
-#pragma unroll
-                    for (int j = 0; j < T::kMB; ++j)
-#pragma unroll
-                        for (int g = 0; g < 4; ++g) {
-                            const float4 w = smem.part[k - 1][wave][(i * T::kMB + j) * 4 + g][lane];
-                            acc[i][j][4 * g] += w.x;
-                            acc[i][j][4 * g + 1] += w.y;
-                            acc[i][j][4 * g + 2] += w.z;
-                            acc[i][j][4 * g + 3] += w.w;
-                        }
-        }
+        read_ops(stage, 1, a1, b1);
+        products(a0, b0);
+        products(a1, b1);
 
         // ---- epilogue: lane (col, half) of block (i, j) holds output columns
         // n0 + 8 g + 4 half + 0..3 (g = 0..3) of token m0 + col, rounded to bf16 and
@@ -491,7 +440,7 @@ __global__ __launch_bounds__(64 * NW, 1) void project_split_kernel(const Project
 // tokens 36.8 / 13.5, 512 tokens 38.7 / 18.5, 1024 tokens 40.2 / 22.8, 2048
 // tokens 40.8 / 40.3; 4096 tokens x 256 columns 39.1 / 21.0; d_model 768, 1024
 // tokens x 768 columns 10.7 / 6.9.
-enum class ProjShape { k256x256, k256x128, k128x128, k64x64, k32x64, k32x32, k16x32, k16x16, k128x128g2, k128x64g2, k128x64g4, k128x64, k64x128g4, k64x128g2, k64x64g4 };
+enum class ProjShape { k256x256, k256x128, k128x128, k64x64, k32x64, k32x32, k16x32, k16x16 };
 
 static long tiles_of(long M, long N, long BN, long BM) { return ((M + BM - 1) / BM) * ((N + BN - 1) / BN); }
 
@@ -515,9 +464,6 @@ long project_tiles(long M, long N) {
         case ProjShape::k32x32: return tiles_of(M, N, 32, 32);
         case ProjShape::k16x32: return tiles_of(M, N, 16, 32);
         case ProjShape::k16x16: return tiles_of(M, N, 16, 16);
-        case ProjShape::k128x64g2: case ProjShape::k128x64g4: case ProjShape::k128x64: return tiles_of(M, N, 128, 64);
-        case ProjShape::k64x128g2: case ProjShape::k64x128g4: return tiles_of(M, N, 64, 128);
-        case ProjShape::k64x64g4: return tiles_of(M, N, 64, 64);
         default: return tiles_of(M, N, 128, 128);
     }
 }
@@ -527,31 +473,10 @@ tk_status launch_project(const ProjectParams& p, hipStream_t st) {
     const dim3 grid((unsigned)launched);
     switch (shape_of(p.M, p.N)) {
         case ProjShape::k256x256:
-            hipLaunchKernelGGL((project_kernel<256, 256, 1>), grid, dim3(ProjTile<256, 256>::kThreads), 0, st, p);
+            hipLaunchKernelGGL((project_kernel<256, 256>), grid, dim3(ProjTile<256, 256>::kThreads), 0, st, p);
             break;
         case ProjShape::k256x128:
-            hipLaunchKernelGGL((project_kernel<256, 128, 1>), grid, dim3(ProjTile<256, 128>::kThreads), 0, st, p);
-            break;
-        case ProjShape::k128x128g2:
-            hipLaunchKernelGGL((project_kernel<128, 128, 2>), grid, dim3((proj_threads<128, 2>())), 0, st, p);
-            break;
-        case ProjShape::k128x64g2:
-            hipLaunchKernelGGL((project_kernel<128, 64, 2>), grid, dim3((proj_threads<128, 2>())), 0, st, p);
-            break;
-        case ProjShape::k128x64g4:
-            hipLaunchKernelGGL((project_kernel<128, 64, 4>), grid, dim3((proj_threads<128, 4>())), 0, st, p);
-            break;
-        case ProjShape::k128x64:
-            hipLaunchKernelGGL((project_kernel<128, 64, 1>), grid, dim3((proj_threads<128, 1>())), 0, st, p);
-            break;
-        case ProjShape::k64x128g4:
-            hipLaunchKernelGGL((project_kernel<64, 128, 4>), grid, dim3((proj_threads<64, 4>())), 0, st, p);
-            break;
-        case ProjShape::k64x128g2:
-            hipLaunchKernelGGL((project_kernel<64, 128, 2>), grid, dim3((proj_threads<64, 2>())), 0, st, p);
-            break;
-        case ProjShape::k64x64g4:
-            hipLaunchKernelGGL((project_kernel<64, 64, 4>), grid, dim3((proj_threads<64, 4>())), 0, st, p);
+            hipLaunchKernelGGL((project_kernel<256, 128>), grid, dim3(ProjTile<256, 128>::kThreads), 0, st, p);
             break;
         case ProjShape::k64x64:
             hipLaunchKernelGGL((project_split_kernel<64, 64, 4, 2>), grid, dim3(256), 0, st, p);
@@ -569,7 +494,7 @@ tk_status launch_project(const ProjectParams& p, hipStream_t st) {
             hipLaunchKernelGGL((project_split_kernel<16, 16, 8, 4>), grid, dim3(512), 0, st, p);
             break;
         default:
-            hipLaunchKernelGGL((project_kernel<128, 128, 1>), grid, dim3(ProjTile<128, 128>::kThreads), 0, st, p);
+            hipLaunchKernelGGL((project_kernel<128, 128>), grid, dim3(ProjTile<128, 128>::kThreads), 0, st, p);
     }
     return hipGetLastError() == hipSuccess ? TK_OK : TK_ERR_HIP;
 }
