@@ -66,17 +66,33 @@ __device__ __forceinline__ void wait_copies(bool next_in_flight) {
 // between the two waves of each SIMD; the smaller ones run 32x32x16 products,
 // each wave reading the next 16-wide k-step's operands during the current one's
 // products.
-template <int BN>
-constexpr int proj_threads() { return 64 * (BN / 64) * 2; }
+//
+// With KG > 1, KG groups of those waves take the k-tiles of one output tile in
+// turn (group g the k-tiles g, g + KG, ...), each through a ring of its own, and
+// group 0 adds up the partial tiles in LDS in group order: for calls whose tiles
+// are too few to fill the CUs with waves.
+template <int BN, int KG>
+constexpr int proj_threads() { return 64 * (BN / 64) * 2 * KG; }
 
-template <int BN, int BM>
-__global__ __launch_bounds__(proj_threads<BN>(), 1) void project_kernel(const ProjectParams p) {
+template <int BN, int BM, int KG>
+union ProjSmem {
+    ProjTile<BN, BM> tile[KG];
+    float4 part[KG - 1 + (KG == 1)][ProjTile<BN, BM>::kWaves][KG == 1 ? 1 : 8 * (BM / 64)][64];  // accumulators as they lie
+};
+
+template <int BN, int BM, int KG>
+__global__ __launch_bounds__((proj_threads<BN, KG>()), 1) void project_kernel(const ProjectParams p) {
     using T = ProjTile<BN, BM>;
     constexpr int kPThreads = T::kThreads, kWCopies = T::kWCopies, kXCopies = T::kXCopies;
     constexpr int kPBN = BN, kPBM = BM;
-    __shared__ T sm;
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    static_assert(KG == 1 || BM < 256, "the ping-pong tiles take all k-tiles");
+    __shared__ ProjSmem<BN, BM, KG> smem;
+    const int lane = threadIdx.x & 63;
+    const int all_wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wave = KG == 1 ? all_wave : all_wave % T::kWaves;  // wave of its k group
+    const int kgrp = KG == 1 ? 0 : all_wave / T::kWaves;
+    const int tid = wave * 64 + lane;
+    T& sm = smem.tile[kgrp];
     const int wn = wave >> 1, wm = wave & 1;  // (BN / 64) x 2 waves over the tile's columns x tokens
     // XCD-aware order: workgroups are dealt to the 8 XCDs round-robin; each XCD
     // takes a contiguous range of tiles, column tiles fastest, so the column
@@ -206,6 +222,8 @@ __global__ __launch_bounds__(proj_threads<BN>(), 1) void project_kernel(const Pr
                 for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
         const int nk = p.K / kPBK;
+        const int nsteps = (nk + KG - 1) / KG;  // every group passes the same barriers; only its last step can be missing
+        auto has = [&](int t) { return t * KG + kgrp < nk; };
         // operand reads of k-step ks of the k-tile in `st`, and the products of one k-step
         auto read_ops = [&](int st, int ks, bf16x8 (&a)[2], bf16x8 (&b)[T::kMB]) {
             const uint16_t* ws = sm.w[st];
@@ -223,9 +241,9 @@ __global__ __launch_bounds__(proj_threads<BN>(), 1) void project_kernel(const Pr
                 for (int j = 0; j < T::kMB; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
         };
-        issue(0, 0);
-        if (nk > 1) issue(1, 1);
-        wait_copies<T::kCopies>(nk > 1);  // this lane's copies of k-tile 0 have landed
+        if (has(0)) issue(kgrp, 0);
+        if (has(1)) issue(KG + kgrp, 1);
+        wait_copies<T::kCopies>(has(1));  // this lane's copies of k-tile 0 have landed
         __syncthreads();      // ... and everyone's
         static_assert(kPBK == 32, "the pipeline below takes two 16-wide k-steps per k-tile");
         // Software pipeline over the k-steps: the operands of the next k-step are
@@ -235,11 +253,11 @@ __global__ __launch_bounds__(proj_threads<BN>(), 1) void project_kernel(const Pr
         bf16x8 a0[2], b0[T::kMB], a1[2], b1[T::kMB];
         read_ops(0, 0, a0, b0);
         int stage = 0;
-        for (int kt = 0; kt + 1 < nk; ++kt) {
+        for (int kt = 0; kt + 1 < nsteps; ++kt) {
             // the stage k-tile kt + 2 goes to was last read before the barrier that
             // ended iteration kt - 1
-            const bool ahead = kt + 2 < nk;
-            if (ahead) issue(kt + 2, stage == 0 ? 2 : stage - 1);
+            const bool ahead = has(kt + 2);
+            if (ahead) issue((kt + 2) * KG + kgrp, stage == 0 ? 2 : stage - 1);
             read_ops(stage, 1, a1, b1);
             products(a0, b0);
             const int next = stage == kStages - 1 ? 0 : stage + 1;
@@ -250,9 +268,42 @@ __global__ __launch_bounds__(proj_threads<BN>(), 1) void project_kernel(const Pr
             stage = next;
         }
         // the last k-tile
-        read_ops(stage, 1, a1, b1);
-        products(a0, b0);
-        products(a1, b1);
+        if (KG == 1 || has(nsteps - 1)) {
+            read_ops(stage, 1, a1, b1);
+            products(a0, b0);
+            products(a1, b1);
+        }
+
+        // ---- k groups: group 0 adds up the partial tiles
+        if constexpr (KG > 1) {
+            __syncthreads();  // every ring is drained
+            if (kgrp > 0) {
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < T::kMB; ++j)
+#pragma unroll
+                        for (int g = 0; g < 4; ++g)
+                            smem.part[kgrp - 1][wave][(i * T::kMB + j) * 4 + g][lane] =
+                                make_float4(acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]);
+            }
+            __syncthreads();
+            if (kgrp > 0) return;
+#pragma unroll 1
+            for (int k = 1; k < KG; ++k)
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < T::kMB; ++j)
+#pragma unroll
+                        for (int g = 0; g < 4; ++g) {
+                            const float4 w = smem.part[k - 1][wave][(i * T::kMB + j) * 4 + g][lane];
+                            acc[i][j][4 * g] += w.x;
+                            acc[i][j][4 * g + 1] += w.y;
+                            acc[i][j][4 * g + 2] += w.z;
+                            acc[i][j][4 * g + 3] += w.w;
+                        }
+        }
 
         // ---- epilogue: lane (col, half) of block (i, j) holds output columns
         // n0 + 8 g + 4 half + 0..3 (g = 0..3) of token m0 + col, rounded to bf16 and
@@ -279,9 +330,9 @@ __global__ __launch_bounds__(proj_threads<BN>(), 1) void project_kernel(const Pr
     }
 }
 
-// Few output tiles (decode steps, short prompts). The tiled kernel above walks
-// all of d_model in each workgroup, k-tile after k-tile, so with few workgroups
-// its time is d_model / 32 memory round trips whatever the token count. Here the
+// The fewest output tiles (decode steps, short prompts). The tiled kernel above
+// walks d_model k-tile after k-tile with a barrier each, so with few workgroups
+// its time is as many memory round trips whatever the token count. Here the
 // output tile is small and the NW waves of a workgroup split d_model instead: a
 // wave takes every NW-th granule of two 32-wide k-steps (128 bytes of each row,
 // a cache line), copies them into a ring of D slots of its own (global->LDS, no
@@ -424,77 +475,84 @@ __global__ __launch_bounds__(64 * NW, 1) void project_split_kernel(const Project
 
 }  // namespace
 
-// Tile shape of a call. For many output tiles the largest that still gives every
-// CU a workgroup: 256 x 256 (8 waves of 64 columns x 128 tokens, one workgroup
-// per CU); else 256 columns x 128 tokens (8 waves of 64 x 64), which serves the
-// narrow thin-key projection (a few KV heads of r columns) over long inputs with
-// the token rows read once; else 128 x 128 (4 waves, two workgroups per CU).
-// Below that the waves split d_model over a small tile (project_split_kernel):
-// the smallest of 16 x 16, 16 x 32, 32 x 32 and 32 x 64 with which every CU has
-// at most one workgroup, since a workgroup's time grows with its columns plus
-// tokens (both are read over all of d_model) as long as CUs are free to take
-// more of them; then 64 x 64 up to two workgroups per CU, beyond which 128 x 128
-// tiles, which read half as much per output, are as fast. Measured (weights from
-// HBM, d_model 4096, N = 1024, us per call, 128 x 128 tiles against the adopted
-// shape): 16 tokens 35.1 / 6.2, 64 tokens 36.3 / 7.3, 128 tokens 36.7 / 9.7, 256
-// tokens 36.8 / 13.5, 512 tokens 38.7 / 18.5, 1024 tokens 40.2 / 22.8, 2048
-// tokens 40.8 / 40.3; 4096 tokens x 256 columns 39.1 / 21.0; d_model 768, 1024
-// tokens x 768 columns 10.7 / 6.9.
-enum class ProjShape { k256x256, k256x128, k128x128, k64x64, k32x64, k32x32, k16x32, k16x16 };
+// Tile shape of a call: the smallest of a ladder of tiles with which every CU gets
+// at most one workgroup. A workgroup's time grows with its columns plus tokens (both
+// are read over all of d_model), so small tiles win as long as CUs are free to take
+// more of them, and a second workgroup on some CUs costs more than the next larger
+// tile on all. Up to 32 x 64 the waves split d_model each for itself
+// (project_split_kernel), from 64 x 64 to 128 x 128 in groups that share a tile's
+// rows (project_kernel with KG > 1); the larger ones take d_model whole.
+// Measured, us per call (weights from HBM), with the shapes of one group only
+// (16 x 16 ... 64 x 64 by single waves, 128 x 128 up to 256 workgroups of the next) /
+// with this ladder:
+//   d_model 4096: 200 x 2048 columns 18.5 / 16.5, 600 x 1024 21.5 / 16.4, 1043 x 1024
+//     35.1 / 23.5, 600 x 2048 42.2 / 23.8, 4500 x 256 33.7 / 22.7, 2202 x 1024
+//     41.5 / 34.6, 9810 x 1024 118 / 97, 3000 x 4096 138 / 105
+//   d_model 768: 1043 x 768 6.5 / 5.8, 2202 x 768 9.8 / 7.5, 6500 x 768 16.9 / 15.2
+// Where a line lies: 32 x 64 against 64 x 64 at 192 and 256 tiles of the former,
+// d_model 4096: 17.2 / 16.0 and 18.5 / 16.5, at 160 16.4 / 15.5, at 136 equal. 64 x 128
+// against 128 x 64 (half the groups, twice the waves to a group): d_model 4096, 1500 x
+// 1024 23.3 / 27.4; 3072, 1500 x 768 19.7 / 21.9; 2048, 1500 x 1024 14.8 / 15.9; 1536,
+// 2202 x 768 11.7 / 10.8; 768, 2202 x 768 8.6 / 7.4. Just past 256 tiles of 256 x 256
+// their last ones run alone, and 256 x 128 are faster: 22000 x 768 from d_model 768
+// 54.3 / 47.2, 9810 x 2048 from 2048 110 / 102, 4500 x 4096 from 4096 200 / 193 (288
+// tiles); at 416 tiles 206 / 258.
+enum class ProjShape { k16x16, k16x32, k32x32, k32x64, k64x64, k64x128, k128x64, k128x128, k256x128, k256x256 };
 
 static long tiles_of(long M, long N, long BN, long BM) { return ((M + BM - 1) / BM) * ((N + BN - 1) / BN); }
 
-static ProjShape shape_of(long M, long N) {
-    if (tiles_of(M, N, 256, 256) >= 256) return ProjShape::k256x256;
-    if (tiles_of(M, N, 256, 128) >= 256) return ProjShape::k256x128;
+static ProjShape shape_of(long M, long N, long K) {
     if (tiles_of(M, N, 16, 16) <= 256) return ProjShape::k16x16;
     if (tiles_of(M, N, 16, 32) <= 256) return ProjShape::k16x32;
     if (tiles_of(M, N, 32, 32) <= 256) return ProjShape::k32x32;
-    if (tiles_of(M, N, 32, 64) <= 256) return ProjShape::k32x64;
-    if (tiles_of(M, N, 64, 64) <= 512) return ProjShape::k64x64;
-    return ProjShape::k128x128;
+    if (tiles_of(M, N, 32, 64) <= 160) return ProjShape::k32x64;
+    if (tiles_of(M, N, 64, 64) <= 256) return ProjShape::k64x64;
+    if (K < 2048 && tiles_of(M, N, 128, 64) <= 256) return ProjShape::k128x64;
+    if (tiles_of(M, N, 64, 128) <= 256) return ProjShape::k64x128;
+    if (tiles_of(M, N, 128, 128) <= 256) return ProjShape::k128x128;
+    if (tiles_of(M, N, 256, 128) <= 256) return ProjShape::k256x128;
+    const long large = tiles_of(M, N, 256, 256);
+    return large > 256 && large <= 320 ? ProjShape::k256x128 : ProjShape::k256x256;
 }
 
-long project_tiles(long M, long N) {
-    switch (shape_of(M, N)) {
-        case ProjShape::k256x256: return tiles_of(M, N, 256, 256);
-        case ProjShape::k256x128: return tiles_of(M, N, 256, 128);
-        case ProjShape::k64x64: return tiles_of(M, N, 64, 64);
-        case ProjShape::k32x64: return tiles_of(M, N, 32, 64);
-        case ProjShape::k32x32: return tiles_of(M, N, 32, 32);
-        case ProjShape::k16x32: return tiles_of(M, N, 16, 32);
+long project_tiles(long M, long N, long K) {
+    switch (shape_of(M, N, K)) {
         case ProjShape::k16x16: return tiles_of(M, N, 16, 16);
-        default: return tiles_of(M, N, 128, 128);
+        case ProjShape::k16x32: return tiles_of(M, N, 16, 32);
+        case ProjShape::k32x32: return tiles_of(M, N, 32, 32);
+        case ProjShape::k32x64: return tiles_of(M, N, 32, 64);
+        case ProjShape::k64x64: return tiles_of(M, N, 64, 64);
+        case ProjShape::k64x128: return tiles_of(M, N, 64, 128);
+        case ProjShape::k128x64: return tiles_of(M, N, 128, 64);
+        case ProjShape::k128x128: return tiles_of(M, N, 128, 128);
+        case ProjShape::k256x128: return tiles_of(M, N, 256, 128);
+        default: return tiles_of(M, N, 256, 256);
     }
 }
 
+template <int BN, int BM, int NW, int D>
+static void run_split(const ProjectParams& p, dim3 grid, hipStream_t st) {
+    hipLaunchKernelGGL((project_split_kernel<BN, BM, NW, D>), grid, dim3(64 * NW), 0, st, p);
+}
+template <int BN, int BM, int KG>
+static void run_tiles(const ProjectParams& p, dim3 grid, hipStream_t st) {
+    hipLaunchKernelGGL((project_kernel<BN, BM, KG>), grid, dim3((proj_threads<BN, KG>())), 0, st, p);
+}
+
 tk_status launch_project(const ProjectParams& p, hipStream_t st) {
-    const long launched = ((long)p.tiles + kXcdCount - 1) / kXcdCount * kXcdCount;
-    const dim3 grid((unsigned)launched);
-    switch (shape_of(p.M, p.N)) {
-        case ProjShape::k256x256:
-            hipLaunchKernelGGL((project_kernel<256, 256>), grid, dim3(ProjTile<256, 256>::kThreads), 0, st, p);
-            break;
-        case ProjShape::k256x128:
-            hipLaunchKernelGGL((project_kernel<256, 128>), grid, dim3(ProjTile<256, 128>::kThreads), 0, st, p);
-            break;
-        case ProjShape::k64x64:
-            hipLaunchKernelGGL((project_split_kernel<64, 64, 4, 2>), grid, dim3(256), 0, st, p);
-            break;
-        case ProjShape::k32x64:
-            hipLaunchKernelGGL((project_split_kernel<32, 64, 8, 2>), grid, dim3(512), 0, st, p);
-            break;
-        case ProjShape::k32x32:
-            hipLaunchKernelGGL((project_split_kernel<32, 32, 8, 4>), grid, dim3(512), 0, st, p);
-            break;
-        case ProjShape::k16x32:
-            hipLaunchKernelGGL((project_split_kernel<16, 32, 8, 4>), grid, dim3(512), 0, st, p);
-            break;
-        case ProjShape::k16x16:
-            hipLaunchKernelGGL((project_split_kernel<16, 16, 8, 4>), grid, dim3(512), 0, st, p);
-            break;
-        default:
-            hipLaunchKernelGGL((project_kernel<128, 128>), grid, dim3(ProjTile<128, 128>::kThreads), 0, st, p);
+    // whole tiles per XCD: tail workgroups of the last XCDs exit at once
+    const dim3 grid((unsigned)((p.tiles + kXcdCount - 1) / kXcdCount * kXcdCount));
+    switch (shape_of(p.M, p.N, p.K)) {
+        case ProjShape::k16x16: run_split<16, 16, 8, 4>(p, grid, st); break;
+        case ProjShape::k16x32: run_split<16, 32, 8, 4>(p, grid, st); break;
+        case ProjShape::k32x32: run_split<32, 32, 8, 4>(p, grid, st); break;
+        case ProjShape::k32x64: run_split<32, 64, 8, 2>(p, grid, st); break;
+        case ProjShape::k64x64: run_tiles<64, 64, 4>(p, grid, st); break;
+        case ProjShape::k64x128: run_tiles<64, 128, 4>(p, grid, st); break;
+        case ProjShape::k128x64: run_tiles<128, 64, 2>(p, grid, st); break;
+        case ProjShape::k128x128: run_tiles<128, 128, 2>(p, grid, st); break;
+        case ProjShape::k256x128: run_tiles<256, 128, 1>(p, grid, st); break;
+        default: run_tiles<256, 256, 1>(p, grid, st);
     }
     return hipGetLastError() == hipSuccess ? TK_OK : TK_ERR_HIP;
 }

@@ -68,6 +68,15 @@ SHAPES = [  # (B, S, d_model, heads, width)
     (2, 170, 288, 33, 28),    # 32 x 64: 9 k-steps, tails
     (1, 1000, 224, 33, 28),   # 64 x 64: 7 k-steps, tails
     (1, 2500, 160, 15, 68),   # 128 x 128: 5 k-tiles, tails
+    # tiles whose k-tiles are shared out among groups of waves
+    (1, 1000, 32, 33, 28),    # 64 x 64: one k-tile for four groups
+    (1, 1000, 288, 33, 28),   # 64 x 64: 9 k-tiles, one group with one more
+    (1, 1500, 96, 33, 28),    # 128 x 64: 3 k-tiles for two groups
+    (3, 200, 2080, 101, 20),  # 64 x 128: 65 k-tiles for four groups
+    (1, 9000, 64, 12, 16),    # 64 x 128, narrow: 2 k-tiles, groups without any
+    (1, 2500, 32, 15, 68),    # 128 x 128: one k-tile for two groups
+    (2, 3000, 96, 15, 68),    # 256 x 128: 3 k-tiles
+    (1, 4700, 96, 64, 68),    # 256 x 256: more than 320 tiles
 ]
 
 
