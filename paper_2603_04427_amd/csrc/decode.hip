@@ -823,8 +823,13 @@ DecodePlan plan_decode(int B, int Hq, int Hkv, int max_ctx, int DV) {
     return pl;
 }
 
-bool deal_splits(int B, int max_ctx, const DecodePlan& pl) {
-    return pl.n_split > 1 && B > 1 && B <= kDealSequences && pl.split_len > kMinSplitTokens &&
+// Two or three sequences of d_v 64 keep equal counts: their streams run at the same
+// rate either way, and what dealing costs itself shows (12 heads, r 16, 4-bit keys:
+// 128950 and 63716 tokens 65.5 us against 67.9 dealt; three up to 90000 from 4 % worse
+// to 8 % better; with four or more it wins, and with d_v 128 from two on: 60000 and
+// 29647 tokens, 32 heads over 8, 48.4 against 41.9).
+bool deal_splits(int B, int max_ctx, int DV, const DecodePlan& pl) {
+    return pl.n_split > 1 && B > (DV == 64 ? 3 : 1) && B <= kDealSequences && pl.split_len > kMinSplitTokens &&
            (long)B * max_ctx <= 1L << 28;
 }
 

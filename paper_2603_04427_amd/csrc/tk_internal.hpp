@@ -48,7 +48,7 @@ DecodePlan plan_decode(int B, int Hq, int Hkv, int max_ctx, int DV);
 // Whether a plan's splits are dealt to the sequences by length: several sequences
 // (at most one a lane) with splits longer than the shortest ever dealt, and round
 // counts whose sums div_small divides exactly.
-bool deal_splits(int B, int max_ctx, const DecodePlan& pl);
+bool deal_splits(int B, int max_ctx, int DV, const DecodePlan& pl);
 
 tk_status launch_decode(const DecodeParams& p, int R, int DV, int HG, int key_format, bool paged,
                         hipStream_t stream);
