@@ -33,7 +33,8 @@
 //    the value product, in place of 16 vector dot products per tile.
 //  * Causal masking only on tiles that cross a wave's diagonal; tiles above it
 //    are skipped. Workgroups are ordered heaviest (longest causal prefix) first
-//    over all KV sequences, and the query blocks of one sequence run on one XCD.
+//    over all KV sequences, and the query blocks of one sequence run on one XCD,
+//    or sequence by sequence where many long ones overflow that XCD's L2.
 #include "tk_device.hpp"
 #include "tk_internal.hpp"
 
@@ -245,6 +246,21 @@ constexpr int prefill_min_blocks(int R, int QC, int KS) { return KS > 1 ? 1 : QC
 // Heads of a KV group per workgroup: as many of gcd(G, 4) as its GW waves hold.
 __host__ __device__ constexpr int heads_per_group(int G, int GW) { return gcd4(G) < GW ? gcd4(G) : GW; }
 
+// Whether the workgroups of an XCD run one sequence after the other instead of the
+// longest walks of all its sequences first: where the query blocks of one sequence
+// fill the XCD's slots (96) twice over and the K and V of the XCD's sequences together
+// exceed its 4 MiB of L2 about four times, so that interleaved walks re-read them from
+// HBM (8192 tokens, r 32, batch 4: 0.47 against 1.57 GB). ms per call, longest first /
+// by sequence, 32 heads over 8, d_v 128: 8 x 6400 tokens r 32 (16.4 MB) 1.626 / 1.584,
+// 4 x 8192 r 128 (16.8 MB) 2.031 / 2.002; on the other side of the line 4 x 8192 r 64
+// (12.6 MB) 1.595 / 1.593, r 32 (10.5 MB) 1.297 / 1.304, 2 x 8192 r 32 0.651 / 0.657.
+constexpr int kXcds = 8;
+template <int R, int DV, int GW, int KS>
+__host__ __device__ constexpr bool prefill_by_sequence(const PrefillParams& p, int pairs, int nqb) {
+    return GW == 4 && KS == 1 && p.causal && pairs % kXcds == 0 && nqb >= 192 &&
+           (long)(pairs / kXcds) * p.Sk * (R + DV) * 2 > 16000000L;
+}
+
 // QC: 32-query column blocks per wave (1 or 2).
 template <int R, int DV, int QC, int GW, int KS>
 __global__ __launch_bounds__(64 * GW * KS, prefill_min_blocks(R, QC, KS)) void prefill_bf16_kernel(
@@ -267,14 +283,19 @@ __global__ __launch_bounds__(64 * GW * KS, prefill_min_blocks(R, QC, KS)) void p
     // to start are the lightest of all; with a multiple of 8 sequences the
     // round-robin dispatch keeps each on one XCD. (Sequence by sequence within each
     // XCD took 191 against 177 us at 2 x 4096 tokens, 32 heads over 8, 46 against
-    // 32 us at 4 x 2048, 12 heads, d_v 64, and the same 1.31 ms at 4 x 8192.)
+    // 32 us at 4 x 2048, 12 heads, d_v 64.) prefill_by_sequence says where it pays.
     const int HPW = heads_per_group(p.G, GW);
     const int RB = GW / HPW;
     const int BM = 32 * QC * RB;
     const int nqb = (p.Sq + BM - 1) / BM;
     const int groups_per_kv = p.G / HPW;
     const int pairs = p.B * p.Hkv * groups_per_kv;
-    const int pair = (int)(blockIdx.x % (unsigned)pairs), rank = (int)(blockIdx.x / (unsigned)pairs);
+    int pair = (int)(blockIdx.x % (unsigned)pairs), rank = (int)(blockIdx.x / (unsigned)pairs);
+    if (prefill_by_sequence<R, DV, GW, KS>(p, pairs, nqb)) {
+        const int logical = (int)(blockIdx.x % kXcds) * (pairs / kXcds * nqb) + (int)(blockIdx.x / kXcds);
+        pair = logical / nqb;
+        rank = logical % nqb;
+    }
     const int qb = p.causal ? nqb - 1 - rank : rank;
     const int b = pair / (p.Hkv * groups_per_kv);
     const int gy = pair % (p.Hkv * groups_per_kv);

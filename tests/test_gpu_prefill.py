@@ -5,6 +5,7 @@ configuration the benchmark times — plus causal invariants."""
 import pytest
 import torch
 
+import paper_2603_04427_amd as tk
 from gpu_cases import device, gate, prefill_on_gpu, prefill_oracle, prefill_rows_oracle, say
 from synth import FULLKEY, WORKLOADS, PrefillSpec, make_prefill, with_shape
 
@@ -125,3 +126,17 @@ def test_causal_future_perturbation_bitwise():
     assert torch.equal(a[:, :, :i + 1], b[:, :, :i + 1])
     assert not torch.equal(a[:, :, i + 1:], b[:, :, i + 1:])
     assert torch.equal(a, prefill_on_gpu(p, spec, dev))   # deterministic
+
+
+@pytest.mark.parametrize("seq,r", [(6300, 32), (6145, 64)])   # just past the line, ragged query blocks
+def test_long_batch_ordered_by_sequence(seq, r):
+    """Eight long sequences run one after the other within each XCD; alone, each runs
+    longest walk first with the same arithmetic, so the rows agree bit for bit."""
+    dev = device()
+    g = torch.Generator(device=dev).manual_seed(seq)
+    q, k, v = (torch.randn(8, h, seq, w, generator=g, device=dev, dtype=torch.bfloat16)
+               for h, w in ((32, r), (8, r), (8, 128)))
+    say(f"prefill by sequence {seq} r {r}")
+    out = tk.tk_attn_prefill(q, k, v)
+    for b in range(8):
+        assert torch.equal(out[b:b + 1], tk.tk_attn_prefill(q[b:b + 1], k[b:b + 1], v[b:b + 1])), b
