@@ -96,7 +96,8 @@ def parse():
 # eight-wave kernels), and the headers every kernel source includes: a change to
 # any of them changes the kernels too.
 EXTRA_SOURCES = {"decode": ("paper_2603_04427_amd/csrc/decode_short.hip",)}
-SHARED_SOURCES = ("paper_2603_04427_amd/csrc/tk_device.hpp", "paper_2603_04427_amd/csrc/tk_internal.hpp")
+SHARED_SOURCES = ("paper_2603_04427_amd/csrc/tk_device.hpp", "paper_2603_04427_amd/csrc/tk_internal.hpp",
+                  "paper_2603_04427_amd/csrc/tk_plan.hpp")
 
 
 def kernel_source_files(kind: str) -> tuple:

@@ -33,8 +33,8 @@
 //    the value product, in place of 16 vector dot products per tile.
 //  * Causal masking only on tiles that cross a wave's diagonal; tiles above it
 //    are skipped. Workgroups are ordered heaviest (longest causal prefix) first
-//    over all KV sequences, and the query blocks of one sequence run on one XCD,
-//    or sequence by sequence where many long ones overflow that XCD's L2.
+//    over all KV sequences, the query blocks of one sequence on one XCD, or
+//    sequence by sequence where that serves K and V from the XCD's L2 (walk_order).
 #include "tk_device.hpp"
 #include "tk_internal.hpp"
 
@@ -47,8 +47,6 @@ namespace tk {
 namespace {
 
 constexpr int kBN = 64;  // keys per tile
-
-__host__ __device__ constexpr int gcd4(int g) { return (g % 4 == 0) ? 4 : (g % 2 == 0 ? 2 : 1); }
 
 typedef short v4s __attribute__((ext_vector_type(4)));
 
@@ -243,24 +241,6 @@ __device__ __forceinline__ bf16x8 vt_operand(const uint16_t* vs, uint32_t vbase,
 // key groups of such waves (KS).
 constexpr int prefill_min_blocks(int R, int QC, int KS) { return KS > 1 ? 1 : QC == 1 ? (R <= 32 ? 3 : 2) : 1; }
 
-// Heads of a KV group per workgroup: as many of gcd(G, 4) as its GW waves hold.
-__host__ __device__ constexpr int heads_per_group(int G, int GW) { return gcd4(G) < GW ? gcd4(G) : GW; }
-
-// Whether the workgroups of an XCD run one sequence after the other instead of the
-// longest walks of all its sequences first: where the query blocks of one sequence
-// fill the XCD's slots (96) twice over and the K and V of the XCD's sequences together
-// exceed its 4 MiB of L2 about four times, so that interleaved walks re-read them from
-// HBM (8192 tokens, r 32, batch 4: 0.47 against 1.57 GB). ms per call, longest first /
-// by sequence, 32 heads over 8, d_v 128: 8 x 6400 tokens r 32 (16.4 MB) 1.626 / 1.584,
-// 4 x 8192 r 128 (16.8 MB) 2.031 / 2.002; on the other side of the line 4 x 8192 r 64
-// (12.6 MB) 1.595 / 1.593, r 32 (10.5 MB) 1.297 / 1.304, 2 x 8192 r 32 0.651 / 0.657.
-constexpr int kXcds = 8;
-template <int R, int DV, int GW, int KS>
-__host__ __device__ constexpr bool prefill_by_sequence(const PrefillParams& p, int pairs, int nqb) {
-    return GW == 4 && KS == 1 && p.causal && pairs % kXcds == 0 && nqb >= 192 &&
-           (long)(pairs / kXcds) * p.Sk * (R + DV) * 2 > 16000000L;
-}
-
 // QC: 32-query column blocks per wave (1 or 2).
 template <int R, int DV, int QC, int GW, int KS>
 __global__ __launch_bounds__(64 * GW * KS, prefill_min_blocks(R, QC, KS)) void prefill_bf16_kernel(
@@ -278,24 +258,15 @@ __global__ __launch_bounds__(64 * GW * KS, prefill_min_blocks(R, QC, KS)) void p
     const int half = lane >> 5, col = lane & 31;
     Tiles<R, DV>& sm = smem.tiles[kgrp];
 
-    // ---- workgroup -> (KV sequence, query block): the heaviest (longest prefix)
-    // block of every sequence, then the next heaviest, so that the last workgroups
-    // to start are the lightest of all; with a multiple of 8 sequences the
-    // round-robin dispatch keeps each on one XCD. (Sequence by sequence within each
-    // XCD took 191 against 177 us at 2 x 4096 tokens, 32 heads over 8, 46 against
-    // 32 us at 4 x 2048, 12 heads, d_v 64.) prefill_by_sequence says where it pays.
+    // ---- workgroup -> (KV sequence, query block), rank 0 the longest prefix (the
+    // orders and where each pays: walk_order)
     const int HPW = heads_per_group(p.G, GW);
     const int RB = GW / HPW;
     const int BM = 32 * QC * RB;
-    const int nqb = (p.Sq + BM - 1) / BM;
-    const int groups_per_kv = p.G / HPW;
-    const int pairs = p.B * p.Hkv * groups_per_kv;
-    int pair = (int)(blockIdx.x % (unsigned)pairs), rank = (int)(blockIdx.x / (unsigned)pairs);
-    if (prefill_by_sequence<R, DV, GW, KS>(p, pairs, nqb)) {
-        const int logical = (int)(blockIdx.x % kXcds) * (pairs / kXcds * nqb) + (int)(blockIdx.x / kXcds);
-        pair = logical / nqb;
-        rank = logical % nqb;
-    }
+    const int nqb = p.blocks, groups_per_kv = p.per_kv;
+    const Place at = place_workgroup(GW == 4 && KS == 1 ? p.order : kRanked, blockIdx.x, p.pairs, nqb);
+    if (at.pair < 0) return;
+    const int pair = at.pair, rank = at.rank;
     const int qb = p.causal ? nqb - 1 - rank : rank;
     const int b = pair / (p.Hkv * groups_per_kv);
     const int gy = pair % (p.Hkv * groups_per_kv);
@@ -610,12 +581,17 @@ __global__ __launch_bounds__(64 * GW * KS, prefill_min_blocks(R, QC, KS)) void p
 }
 
 template <int R, int DV, int GW, int KS>
-static hipError_t run(const PrefillParams& p, hipStream_t st) {
+static hipError_t run(PrefillParams p, hipStream_t st) {
     const int HPW = heads_per_group(p.G, GW);
     const int BM = 32 * (GW / HPW);
-    const long nqb = (p.Sq + BM - 1) / BM;
-    const long groups = nqb * p.Hkv * (p.G / HPW) * p.B;
+    const long nqb = ((long)p.Sq + BM - 1) / BM, pairs = (long)p.B * p.Hkv * (p.G / HPW);
+    p.order = GW == 4 && KS == 1 ? walk_order({p.B, p.Hkv, p.G, p.Sq, p.Sk, R, DV, p.causal != 0}, prefill_min_blocks(R, 1, KS))
+                                 : kRanked;
+    const long groups = order_launch(p.order, nqb * pairs);
     if (groups > 0x7fffffffL) return hipErrorInvalidValue;
+    p.pairs = (int)pairs;
+    p.blocks = (int)nqb;
+    p.per_kv = p.G / HPW;
     hipLaunchKernelGGL((prefill_bf16_kernel<R, DV, 1, GW, KS>), dim3((unsigned)groups), dim3(64 * GW * KS), 0, st, p);
     return hipGetLastError();
 }

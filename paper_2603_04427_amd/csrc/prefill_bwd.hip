@@ -37,12 +37,6 @@ namespace tk {
 namespace {
 
 constexpr int kT = 64;  // keys (dq kernel) or query rows (dk/dv kernel, or half as many) per LDS tile
-constexpr int kXcds = 8;
-
-__host__ __device__ constexpr int gcd4(int g) { return (g % 4 == 0) ? 4 : (g % 2 == 0 ? 2 : 1); }
-
-// Heads of a KV group per workgroup: as many of gcd(G, 4) as its GW waves hold.
-__host__ __device__ constexpr int heads_per_group(int G, int GW) { return gcd4(G) < GW ? gcd4(G) : GW; }
 
 typedef short v4s __attribute__((ext_vector_type(4)));
 
@@ -255,17 +249,14 @@ __global__ __launch_bounds__(64 * GW * KS, KS == 1 ? 2 : 1) void bwd_dq_kernel(c
     DqTiles<R, DV>& sm = smem.tiles[kgrp];
     const int half = lane >> 5, col = lane & 31;
 
-    // workgroup -> (KV sequence, 32 rows x HPW heads): the heaviest block of every
-    // sequence, then the next heaviest, so that the last workgroups to start are
-    // the lightest of all; with a multiple of 8 sequences the round-robin dispatch
-    // keeps each on one XCD
+    // workgroup -> (KV sequence, 32 rows x HPW heads), rank 0 the longest walk (walk_order)
     const int HPW = heads_per_group(p.G, GW);
     const int RB = GW / HPW;
     const int BM = 32 * RB;
-    const int nqb = (p.Sq + BM - 1) / BM;
-    const int groups_per_kv = p.G / HPW;
-    const int pairs = p.B * p.Hkv * groups_per_kv;
-    const int pair = (int)(blockIdx.x % (unsigned)pairs), rank = (int)(blockIdx.x / (unsigned)pairs);
+    const int nqb = p.blocks, groups_per_kv = p.per_kv;
+    const Place at = place_workgroup(GW == 4 && KS == 1 ? p.order : kRanked, blockIdx.x, p.pairs, nqb);
+    if (at.pair < 0) return;
+    const int pair = at.pair, rank = at.rank;
     const int qb = p.causal ? nqb - 1 - rank : rank;
     const int b = pair / (p.Hkv * groups_per_kv);
     const int gy = pair % (p.Hkv * groups_per_kv);
@@ -451,20 +442,6 @@ __device__ __forceinline__ void issue_qtile(const PrefillBwdParams& p, KvTiles<R
     }
 }
 
-// Order of the dK/dV workgroups. Longest first over all sequences balances the
-// CUs: with the workgroups of one sequence after the other, a CU's two resident
-// workgroups were both of the longest or both of the shortest (606 against 522 us
-// at 2 x 4096 tokens, 954 against 723 us at 4 x 4096; r 32, d_v 128, 32 query
-// heads over 8). Where the key blocks of one sequence fill an XCD by themselves
-// (64 slots) and read the same G heads' tiles, keeping to one sequence at a time
-// serves those reads from its L2: 2.84 against 2.95 ms at 4 x 8192. With r + d_v of
-// 192 or more (one workgroup per CU, more work per byte) the balance counts more
-// (5.50 against 5.73 ms there at r 128), and with G = 1 as well (1.40 against
-// 1.42 ms at 2 x 8192, 32 heads).
-__host__ __device__ constexpr bool bwd_by_sequence(int R, int DV, int G, int nkb, int KW) {
-    return R + DV < 192 && KW == 4 && G >= 4 && nkb >= 64;
-}
-
 // Register budget: the dK and dV accumulators (r + d_v per lane) and the K and V
 // rows fit two waves per SIMD while r + d_v < 192.
 template <int R, int DV, int KW, int QG, int T>
@@ -481,18 +458,10 @@ __global__ __launch_bounds__(64 * KW * QG, R + DV >= 192 || KW * QG > 4 ? 1 : 2)
     KvTiles<R, DV, T>& sm = smem.tiles[qgrp];
     const int half = lane >> 5, col = lane & 31;
 
-    // workgroup -> (KV sequence, KB keys), longest query range first: over all
-    // sequences as in the dQ kernel, or sequence by sequence (bwd_by_sequence)
-    const int nkb = (p.Sk + KB - 1) / KB;
-    const int pairs = p.B * p.Hkv;
-    int pair = (int)(blockIdx.x % (unsigned)pairs), kbi = (int)(blockIdx.x / (unsigned)pairs);
-    if (bwd_by_sequence(R, DV, p.G, nkb, KW)) {
-        const int n = pairs * nkb, per_xcd = (n + kXcds - 1) / kXcds;
-        const int logical = (int)(blockIdx.x % kXcds) * per_xcd + (int)(blockIdx.x / kXcds);
-        if (logical >= n) return;
-        pair = logical / nkb;
-        kbi = logical % nkb;
-    }
+    // workgroup -> (KV sequence, KB keys), rank 0 the longest query range (dkdv_order)
+    const Place at = place_workgroup(KW == 4 ? p.order : kRanked, blockIdx.x, p.pairs, p.blocks);
+    if (at.pair < 0) return;
+    const int pair = at.pair, kbi = at.rank;
     const int b = pair / p.Hkv, g = pair % p.Hkv;
     const int k0g = kbi * KB;              // first key of the workgroup
     const int k0 = k0g + wave * 32;        // first key of the wave
@@ -640,11 +609,20 @@ __global__ __launch_bounds__(64 * KW * QG, R + DV >= 192 || KW * QG > 4 ? 1 : 2)
 
 // ------------------------------------------------------------------ dispatch
 
+static AttnSizes sizes_of(const PrefillBwdParams& p, int R, int DV) {
+    return {p.B, p.Hkv, p.G, p.Sq, p.Sk, R, DV, p.causal != 0};
+}
+
 template <int R, int DV, int GW, int KS>
-static hipError_t run_dq(const PrefillBwdParams& p, hipStream_t st) {
+static hipError_t run_dq(PrefillBwdParams p, hipStream_t st) {
     const int HPW = heads_per_group(p.G, GW);
     const int BM = 32 * (GW / HPW);
-    const long groups = (long)((p.Sq + BM - 1) / BM) * p.Hkv * (p.G / HPW) * p.B;
+    const long nqb = ((long)p.Sq + BM - 1) / BM, pairs = (long)p.B * p.Hkv * (p.G / HPW);
+    p.order = GW == 4 && KS == 1 ? walk_order(sizes_of(p, R, DV), 2) : kRanked;
+    p.pairs = (int)pairs;
+    p.blocks = (int)nqb;
+    p.per_kv = p.G / HPW;
+    const long groups = order_launch(p.order, nqb * pairs);
     if (groups * 64 * GW * KS > 0xffffffffL) return hipErrorInvalidValue;
     if (groups == 0) return hipSuccess;
     hipLaunchKernelGGL((bwd_dq_kernel<R, DV, GW, KS>), dim3((unsigned)groups), dim3(64 * GW * KS), 0, st, p);
@@ -652,10 +630,13 @@ static hipError_t run_dq(const PrefillBwdParams& p, hipStream_t st) {
 }
 
 template <int R, int DV, int KW, int QG, int T>
-static hipError_t run_dkdv(const PrefillBwdParams& p, hipStream_t st) {
-    const long nkb = (p.Sk + 32 * KW - 1) / (32 * KW);
-    long groups = nkb * p.Hkv * p.B;
-    if (bwd_by_sequence(R, DV, p.G, (int)nkb, KW)) groups = (groups + kXcds - 1) / kXcds * kXcds;
+static hipError_t run_dkdv(PrefillBwdParams p, hipStream_t st) {
+    const long nkb = ((long)p.Sk + 32 * KW - 1) / (32 * KW), pairs = (long)p.B * p.Hkv;
+    p.order = dkdv_order(sizes_of(p, R, DV), KW);
+    p.pairs = (int)pairs;
+    p.blocks = (int)nkb;
+    p.per_kv = 1;
+    const long groups = order_launch(p.order, nkb * pairs);
     if (groups * 64 * KW * QG > 0xffffffffL) return hipErrorInvalidValue;
     if (groups == 0) return hipSuccess;
     hipLaunchKernelGGL((bwd_dkdv_kernel<R, DV, KW, QG, T>), dim3((unsigned)groups), dim3(64 * KW * QG), 0, st, p);

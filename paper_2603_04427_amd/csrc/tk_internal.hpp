@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "tk_attn.h"
+#include "tk_plan.hpp"
 
 namespace tk {
 
@@ -86,6 +87,10 @@ struct PrefillParams {
     float* lse;      // [B, Hq, Sq] natural-log log-sum-exp of the scaled scores, or null (bf16 only)
     int B, Hq, Hkv, G, Sq, Sk;
     int causal;
+    int order;       // of the workgroups (Order), which take pairs x blocks walks,
+    int pairs;       // per_kv pairs to a KV sequence
+    int blocks;
+    int per_kv;
     float qscale;    // softmax scale * log2(e)
 };
 
@@ -104,6 +109,10 @@ struct PrefillBwdParams {
     float* lse2;        // [B, Hq, Sq] workspace: the rows' log-sum-exp in log2 units
     int B, Hq, Hkv, G, Sq, Sk;
     int causal;
+    int order;          // of the kernel's workgroups (Order), which take pairs x blocks walks,
+    int pairs;          // per_kv pairs to a KV sequence
+    int blocks;
+    int per_kv;
     float scale;        // softmax scale
     float qscale;       // scale * log2(e)
 };

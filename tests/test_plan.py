@@ -1,0 +1,118 @@
+"""The rules that pick a kernel's form from a call's sizes (csrc/tk_plan.hpp), compiled
+for the host: every order gives each piece of work to one workgroup, keeps a KV
+sequence on one XCD where it says so, and lies where the measurements put it."""
+import ctypes
+import itertools
+import os
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2603_04427_amd", "csrc")
+
+RANKED, OWNED, BY_SEQUENCE = 0, 1, 2
+
+QUERIES = r"""
+#include "tk_plan.hpp"
+using namespace tk;
+extern "C" {
+void place(int order, int block, int pairs, int n, int* out) {
+    const Place p = place_workgroup(order, block, pairs, n);
+    out[0] = p.pair;
+    out[1] = p.rank;
+}
+long launched(int order, long workgroups) { return order_launch(order, workgroups); }
+int walks(int B, int Hq, int Hkv, int Sq, int Sk, int r, int dv, int causal, int slots) {
+    return walk_order({B, Hkv, Hq / Hkv, Sq, Sk, r, dv, causal != 0}, slots);
+}
+int dkdv(int B, int Hq, int Hkv, int Sq, int Sk, int r, int dv, int causal, int KW) {
+    return dkdv_order({B, Hkv, Hq / Hkv, Sq, Sk, r, dv, causal != 0}, KW);
+}
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def plan(tmp_path_factory):
+    d = tmp_path_factory.mktemp("plan")
+    src, lib = d / "queries.cpp", d / "queries.so"
+    src.write_text(QUERIES)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-I" + CSRC, str(src), "-o", str(lib)],
+                   check=True)
+    return ctypes.CDLL(str(lib))
+
+
+def places(plan, order, pairs, n):
+    out = (ctypes.c_int * 2)()
+    for block in range(plan.launched(order, ctypes.c_long(pairs * n))):
+        plan.place(order, block, pairs, n, out)
+        yield block, out[0], out[1]
+
+
+@pytest.mark.parametrize("order", [RANKED, OWNED, BY_SEQUENCE])
+def test_every_order_places_each_walk_once(plan, order):
+    for pairs, n in itertools.product((1, 3, 7, 8, 12, 16, 20, 24, 56, 64, 104), (1, 2, 3, 5, 8, 13, 64)):
+        if order == OWNED and pairs % 8:
+            continue
+        seen = [(pair, rank) for _, pair, rank in places(plan, order, pairs, n) if pair >= 0]
+        assert sorted(seen) == [(p, r) for p in range(pairs) for r in range(n)]
+
+
+@pytest.mark.parametrize("order", [RANKED, OWNED, BY_SEQUENCE])
+def test_longest_walks_start_first_on_each_xcd(plan, order):
+    """Ranks rise over an XCD's workgroups: over all its pairs, or pair by pair."""
+    for pairs, n in ((8, 5), (16, 4), (24, 7), (56, 3)):
+        for xcd in range(8):
+            mine = [(pair, rank) for block, pair, rank in places(plan, order, pairs, n) if block % 8 == xcd and pair >= 0]
+            assert mine == sorted(mine, key=(lambda w: w) if order == BY_SEQUENCE else (lambda w: w[1]))
+
+
+@pytest.mark.parametrize("B,Hq,Hkv", [(2, 64, 8), (8, 28, 4), (8, 40, 5), (16, 6, 1), (4, 48, 8), (24, 32, 2)])
+def test_head_groups_of_a_kv_sequence_share_an_xcd(plan, B, Hq, Hkv):
+    """Several head groups read the same K and V: no order that such a call takes may spread
+    them over the XCDs while the pairs divide among these."""
+    G = Hq // Hkv
+    per_kv = G // next(h for h in (4, 2, 1) if G % h == 0)
+    pairs = B * Hkv * per_kv
+    assert per_kv > 1 and pairs % 8 == 0
+    for S, causal, r in itertools.product((300, 1000, 4096), (0, 1), (32, 128)):
+        order = plan.walks(B, Hq, Hkv, S, S, r, 128, causal, 3 if r == 32 else 2)
+        n = -(-S // 128)
+        xcds = {}
+        for block, pair, _ in places(plan, order, pairs, n):
+            if pair >= 0:
+                xcds.setdefault(pair // per_kv, set()).add(block % 8)
+        # an eighth of the pairs may end inside a sequence: it then has two neighbours' XCDs
+        assert sum(len(x) for x in xcds.values()) <= len(xcds) + 7
+
+
+@pytest.mark.parametrize("call,slots,order", [
+    ((2, 32, 8, 4096, 4096, 32, 128, 1), 3, RANKED),
+    ((2, 32, 8, 8192, 8192, 32, 128, 1), 3, RANKED),
+    ((4, 32, 8, 8192, 8192, 32, 128, 1), 3, BY_SEQUENCE),    # K and V over 6 MB an XCD, blocks fill it
+    ((8, 32, 8, 6400, 6400, 32, 128, 1), 3, BY_SEQUENCE),
+    ((4, 64, 8, 8192, 8192, 32, 128, 1), 3, BY_SEQUENCE),
+    ((2, 64, 8, 4096, 4096, 32, 128, 1), 3, OWNED),
+    ((4, 32, 32, 8192, 8192, 32, 128, 1), 3, BY_SEQUENCE),   # 42 MB an XCD, one head per KV sequence
+    ((2, 32, 32, 8192, 8192, 32, 128, 1), 3, RANKED),        # 21 MB
+    ((8, 32, 32, 2048, 2048, 32, 128, 0), 3, BY_SEQUENCE),   # equal walks
+    ((4, 32, 32, 4096, 4096, 32, 128, 0), 3, BY_SEQUENCE),
+    ((16, 32, 8, 1024, 1024, 32, 128, 0), 3, BY_SEQUENCE),
+    ((1, 12, 12, 8192, 8192, 16, 64, 1), 3, RANKED),
+    ((9, 28, 4, 5381, 5381, 32, 128, 1), 3, BY_SEQUENCE),    # 252 pairs, G 7, 7.8 MB
+    ((2, 40, 5, 6000, 6000, 32, 128, 1), 3, RANKED),         # 20 pairs, 2.4 MB
+    ((25, 40, 5, 123, 127, 128, 128, 1), 2, BY_SEQUENCE),
+])
+def test_order_of_measured_calls(plan, call, slots, order):
+    assert plan.walks(*call, slots) == order
+
+
+@pytest.mark.parametrize("call,order", [
+    ((2, 32, 8, 4096, 4096, 32, 128, 1), RANKED),
+    ((4, 32, 8, 8192, 8192, 32, 128, 1), BY_SEQUENCE),
+    ((4, 32, 8, 8192, 8192, 128, 128, 1), RANKED),
+    ((19, 32, 32, 2295, 2295, 32, 128, 0), BY_SEQUENCE),
+])
+def test_dkdv_order_of_measured_calls(plan, call, order):
+    assert plan.dkdv(*call, 4) == order
+    assert plan.dkdv(*call, 2) == RANKED  # two keys blocks a workgroup: few of them
