@@ -12,7 +12,7 @@
 //    KV group and 4 / HPW row blocks, so each K/V tile in LDS serves every wave.
 //    Calls with too few rows to fill the part take fewer waves per tile (GW) and
 //    several key groups of such waves (KS), which walk the tiles in turn with
-//    tiles of their own and merge in LDS (the rule is above the dispatch).
+//    tiles of their own and merge in LDS (the rule: prefill_form).
 //  * 64-key tiles are double-buffered in LDS and filled straight from global
 //    memory (global_load_lds, 16 bytes per lane, issued a whole tile ahead and
 //    awaited only before the barrier that publishes the tile), K and V both in their memory
@@ -580,13 +580,16 @@ __global__ __launch_bounds__(64 * GW * KS, prefill_min_blocks(R, QC, KS)) void p
     }
 }
 
+static AttnSizes sizes_of(const PrefillParams& p, int R, int DV) {
+    return {p.B, p.Hkv, p.G, p.Sq, p.Sk, R, DV, p.causal != 0};
+}
+
 template <int R, int DV, int GW, int KS>
 static hipError_t run(PrefillParams p, hipStream_t st) {
     const int HPW = heads_per_group(p.G, GW);
     const int BM = 32 * (GW / HPW);
     const long nqb = ((long)p.Sq + BM - 1) / BM, pairs = (long)p.B * p.Hkv * (p.G / HPW);
-    p.order = GW == 4 && KS == 1 ? walk_order({p.B, p.Hkv, p.G, p.Sq, p.Sk, R, DV, p.causal != 0}, prefill_min_blocks(R, 1, KS))
-                                 : kRanked;
+    p.order = GW == 4 && KS == 1 ? walk_order(sizes_of(p, R, DV), prefill_min_blocks(R, 1, KS)) : kRanked;
     const long groups = order_launch(p.order, nqb * pairs);
     if (groups > 0x7fffffffL) return hipErrorInvalidValue;
     p.pairs = (int)pairs;
@@ -596,49 +599,14 @@ static hipError_t run(PrefillParams p, hipStream_t st) {
     return hipGetLastError();
 }
 
-// Workgroup shape of a call. A unit is one wave's rows: 32 query rows of one head.
-// With four units per workgroup and one wave per unit, a call of few units leaves
-// CUs idle and gives a busy CU's SIMDs one wave each, which exposes the tile's
-// dependent score -> softmax -> value chain (0.9 us per 64-key tile against 0.35
-// with three waves per SIMD). Key groups split that walk; fewer waves per tile
-// spread the units over more CUs, at the price of more tile copies:
-//   up to 256 units    one unit per workgroup, as many key groups as the LDS holds (up to 4)
-//   up to 512          two units, as many key groups (up to 4)
-//   up to 1280         two units x 2 where two workgroups share a CU's LDS
-//                      (r + d_v <= 160); else, and up to 1024 units where every row
-//                      walks about the same number of keys (no causal ramp to
-//                      balance) over wide values, so that sharing the tiles
-//                      counts, four units x 2
-//   up to 1536         two units x 2 for d_v 64 (three workgroups per CU)
-//   up to 2048         as up to 1280 for long walks on a causal ramp (20 tiles or more)
-//   beyond             four units, one key group
-// A walk of one tile has nothing to split, and one of two or three tiles is split
-// in two at most. Measured, us per call, four units x 1 against the adopted shape
-// (r 32, d_v 128 unless stated; 32 query heads over 8 KV heads):
-//   128 queries over 8192 keys     111.6 / 44.3      500 over 7700     103.4 / 52.6
-//   1000 over 8000                 107.5 / 90.1      1100 causal        21.0 / 15.4
-//   2048 causal                     36.9 / 35.4      r 128, 500 over 7700  145.4 / 91.7
-//   12 heads, r 32, d_v 64: 2 x 500 causal 9.6 / 7.0; 4096 causal 48.9 / 32.9
-// and, on the other side of the lines, 2 x 1024 causal 22.2 against 23.4 with two
-// units x 2, 2000 over 8000 158 / 170, 4 x 512 causal 15.1 / 17.2; 8 x 1000 causal,
-// 12 heads, d_v 64, 21.2 / 21.7 (r 64: 23.9 / 28.7).
 template <int R, int DV>
 static hipError_t run(const PrefillParams& p, hipStream_t st) {
-    constexpr int kGroupLds = (int)sizeof(Tiles<R, DV>);
-    constexpr int kMost = 160 * 1024 / kGroupLds < 4 ? 160 * 1024 / kGroupLds : 4;  // key groups in one CU's LDS
-    constexpr bool kPair = 4 * kGroupLds <= 160 * 1024;  // two workgroups of two key groups share a CU
-    const long units = (long)p.B * p.Hq * ((p.Sq + 31) / 32);
-    const long tiles = ((long)p.Sk + kBN - 1) / kBN;
-    const bool even = !p.causal || p.Sk - p.Sq >= p.Sq;  // every row walks about as many keys
-    if (tiles >= 2) {
-        if (units <= 512 && tiles < 4) return run<R, DV, 2, 2>(p, st);
-        if (units <= 256) return run<R, DV, 1, kMost>(p, st);
-        if (units <= 512) return run<R, DV, 2, kMost>(p, st);
-        const bool ramp = !even && (units <= 1280 || (units <= 2048 && tiles >= 20));
-        if (kPair && (DV == 64 ? units <= 1536 : ramp)) return run<R, DV, 2, 2>(p, st);
-        if (!(kPair && DV == 64) && tiles >= 8 && (ramp || units <= 1024)) return run<R, DV, 4, 2>(p, st);
-    }
-    return run<R, DV, 4, 1>(p, st);
+    constexpr int kMost = prefill_most_groups(R, DV);
+    static_assert(prefill_tile_lds(R, DV) == sizeof(Tiles<R, DV>), "the plan's LDS is the kernel's");
+    const PrefillForm f = prefill_form(sizes_of(p, R, DV));
+    if (f.waves == 1) return run<R, DV, 1, kMost>(p, st);
+    if (f.waves == 4) return f.groups == 1 ? run<R, DV, 4, 1>(p, st) : run<R, DV, 4, 2>(p, st);
+    return f.groups == 2 ? run<R, DV, 2, 2>(p, st) : run<R, DV, 2, kMost>(p, st);
 }
 
 template <int R>

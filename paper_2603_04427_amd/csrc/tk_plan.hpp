@@ -101,4 +101,80 @@ constexpr int dkdv_order(const AttnSizes& s, int KW) {
     return KW == 4 && (!s.causal || (s.r + s.dv < 192 && s.G >= 4 && nkb >= 64)) ? kBySequence : kRanked;
 }
 
+// ------------------------------------------------------------------ forward: workgroup shape
+//
+// A unit is one wave's rows: 32 query rows of one head. With four units per workgroup
+// and one wave per unit, a call of few units leaves CUs idle and gives a busy CU's SIMDs
+// one wave each, which exposes the tile's dependent score -> softmax -> value chain (0.9
+// us per 64-key tile against 0.35 with three waves per SIMD). Key groups split that
+// walk; fewer waves per tile spread the units over more CUs, at the price of more tile
+// copies and, where the workgroups no longer fit the CUs at once, of a second round.
+struct PrefillForm {
+    int waves, groups;  // waves that share a tile, key groups of them that walk the tiles in turn
+};
+
+// Walks of about the same length for every row: no mask, or a prefix at least as long as
+// the rows are many.
+constexpr bool even_walks(const AttnSizes& s) { return !s.causal || s.Sk - s.Sq >= s.Sq; }
+// Workgroups of GW units a key group (rows and heads past the end included).
+constexpr long row_workgroups(const AttnSizes& s, int GW) {
+    const int heads = heads_per_group(s.G, GW), rows = 32 * (GW / heads);
+    return (long)s.B * s.Hkv * (s.G / heads) * (((long)s.Sq + rows - 1) / rows);
+}
+// LDS of one key group's two K and V tiles, and the most key groups in one CU's LDS (up to 4).
+constexpr int prefill_tile_lds(int r, int dv) { return 2 * 64 * (r + dv) * 2; }
+constexpr int prefill_most_groups(int r, int dv) {
+    return 160 * 1024 / prefill_tile_lds(r, dv) < 4 ? 160 * 1024 / prefill_tile_lds(r, dv) : 4;
+}
+
+//   up to 256 units    one unit per workgroup, as many key groups as the LDS holds
+//   up to 512          two units, as many key groups, in at most 256 workgroups (one a CU)
+//   up to 1280         two units x 2 where two workgroups share a CU's LDS
+//                      (r + d_v <= 160); else, and up to 1024 units in 256 workgroups
+//                      where every row walks about the same number of keys (no causal
+//                      ramp to balance) over wide values, so that sharing the tiles
+//                      counts, four units x 2
+//   up to 1536         two units x 2 for d_v 64, three workgroups per CU (r 64: two)
+//   up to 2048         as up to 1280 for long walks on a causal ramp (20 tiles or more)
+//   beyond             four units, one key group
+// A walk of one tile has nothing to split, and one of two or three tiles is split in two
+// at most. Where splitting leaves no room on the CUs at once (two units x 2: two a CU at r
+// + d_v 128 and 160, three below), the walk has to be a ramp of 8 tiles or more; at r +
+// d_v 160 one of under 4 tiles is split in up to 256 workgroups; and equal walks of under
+// 6 tiles that already fit the CUs whole stay whole. Measured, us per call, four units x 1 against the
+// adopted shape (r 32, d_v 128 unless stated; 32 query heads over 8 KV heads):
+//   128 queries over 8192 keys     111.6 / 44.3      500 over 7700     103.4 / 52.6
+//   1000 over 8000                 107.5 / 90.1      1100 causal        21.0 / 15.4
+//   2048 causal                     36.9 / 35.4      r 128, 500 over 7700  145.4 / 91.7
+//   12 heads, r 32, d_v 64: 2 x 500 causal 9.6 / 7.0; 4096 causal 48.9 / 32.9
+// and, on the other side of the lines, the shape not taken second: 2 x 1024 causal 22.2 /
+// 23.4 with two units x 2, 2000 over 8000 158 / 170, 4 x 512 causal 15.1 / 17.2; 8 x 1000
+// causal, 12 heads, d_v 64, 21.2 / 21.7 (r 64: 23.9 / 28.7). Short walks: 5 x 207 causal
+// 8.8 / 12.0, 5 x 265 9.3 / 11.9, 28 heads over 4, 15 x 71 8.2 / 11.5 (two units x 2); 9 x
+// 178, r 16, 32 heads over 4 of d_v 64, 3 tiles 7.7 / 8.8; 32 heads, r 64, 5 x 94 6.8 / 8.8
+// (320 workgroups of two units x 3); 32 over 4 of d_v 64, r 64, 9 x 158 8.2 / 10.4; equal walks in 392 workgroups: 28 over 4, 7 x 131
+// over 508 16.2 / 20.0 (four units x 2).
+constexpr PrefillForm prefill_form(const AttnSizes& s) {
+    const int most = prefill_most_groups(s.r, s.dv);
+    const bool pair = 4 * prefill_tile_lds(s.r, s.dv) <= 160 * 1024;  // two workgroups of two key groups share a CU
+    const long units = (long)s.B * s.Hkv * s.G * (((long)s.Sq + 31) / 32);
+    const long tiles = ((long)s.Sk + 63) / 64, two = row_workgroups(s, 2), four = row_workgroups(s, 4);
+    const bool even = even_walks(s);
+    if (tiles < 2) return {4, 1};
+    if (units <= 512 && tiles < 4 && two <= 256) return {2, 2};
+    if (units <= 256) return {1, most};
+    if (units <= 512 && tiles >= 4 && two <= 256) return {2, most};
+    if (pair && s.dv == 64) {
+        const bool resident = two <= (s.r < 64 ? 768 : 512) || (!even && tiles >= 8);
+        return units <= 1536 && resident && !(even && two > 256 && four <= 256 && tiles < 6) ? PrefillForm{2, 2}
+                                                                                            : PrefillForm{4, 1};
+    }
+    if (!even && (units <= 1280 || (units <= 2048 && tiles >= 20))) {
+        if (pair && two <= (tiles >= 8 ? 2048 : tiles >= 4 ? 512 : 256)) return {2, 2};
+        if (!pair && tiles >= 8) return {4, 2};
+    }
+    if (even && tiles >= 8 && units <= 1024 && four <= 256) return {4, 2};
+    return {4, 1};
+}
+
 }  // namespace tk

@@ -25,6 +25,10 @@ long launched(int order, long workgroups) { return order_launch(order, workgroup
 int walks(int B, int Hq, int Hkv, int Sq, int Sk, int r, int dv, int causal, int slots) {
     return walk_order({B, Hkv, Hq / Hkv, Sq, Sk, r, dv, causal != 0}, slots);
 }
+int form(int B, int Hq, int Hkv, int Sq, int Sk, int r, int dv, int causal) {
+    const PrefillForm f = prefill_form({B, Hkv, Hq / Hkv, Sq, Sk, r, dv, causal != 0});
+    return f.waves * 10 + f.groups;
+}
 int dkdv(int B, int Hq, int Hkv, int Sq, int Sk, int r, int dv, int causal, int KW) {
     return dkdv_order({B, Hkv, Hq / Hkv, Sq, Sk, r, dv, causal != 0}, KW);
 }
@@ -116,3 +120,32 @@ def test_order_of_measured_calls(plan, call, slots, order):
 def test_dkdv_order_of_measured_calls(plan, call, order):
     assert plan.dkdv(*call, 4) == order
     assert plan.dkdv(*call, 2) == RANKED  # two keys blocks a workgroup: few of them
+
+
+@pytest.mark.parametrize("call,form", [
+    ((1, 32, 8, 128, 8192, 32, 128, 1), 14),
+    ((1, 32, 8, 500, 7700, 32, 128, 1), 24),
+    ((1, 32, 8, 500, 7700, 128, 128, 1), 22),
+    ((1, 32, 8, 1000, 8000, 32, 128, 1), 42),
+    ((1, 32, 8, 1100, 1100, 32, 128, 1), 22),
+    ((1, 32, 8, 2048, 2048, 32, 128, 1), 22),
+    ((1, 12, 12, 4096, 4096, 32, 64, 1), 22),
+    ((2, 32, 8, 1024, 1024, 32, 128, 1), 41),
+    ((4, 32, 8, 512, 512, 32, 128, 1), 41),
+    ((5, 32, 8, 207, 207, 32, 128, 1), 41),      # 4 tiles in 560 workgroups of two units
+    ((5, 32, 8, 265, 265, 32, 128, 1), 41),
+    ((15, 28, 4, 71, 71, 32, 128, 1), 41),       # G 7: rows past the end in every workgroup
+    ((11, 6, 1, 244, 244, 32, 128, 1), 22),      # 4 tiles in 264 workgroups: one round
+    ((5, 32, 32, 94, 94, 64, 128, 0), 41),       # 320 workgroups that fill a CU each
+    ((7, 28, 4, 131, 508, 32, 128, 0), 41),      # equal walks in 392 workgroups of four units
+    ((4, 8, 2, 1024, 1086, 32, 128, 0), 42),     # in 256
+    ((4, 32, 4, 169, 169, 64, 64, 0), 41),       # equal walks of 3 tiles, all resident whole
+    ((3, 32, 4, 225, 225, 16, 64, 1), 22),
+    ((9, 32, 4, 158, 158, 64, 64, 1), 41),       # 720 workgroups of two units, two a CU
+    ((15, 12, 12, 188, 1995, 64, 64, 1), 41),    # 540, equal walks
+    ((5, 28, 4, 71, 108, 32, 128, 1), 41),       # 2 tiles in 280 workgroups
+    ((4, 32, 8, 8192, 8192, 32, 128, 1), 41),
+    ((1, 32, 8, 64, 64, 32, 128, 1), 41),        # one tile
+])
+def test_prefill_form_of_measured_calls(plan, call, form):
+    assert plan.form(*call) == form
