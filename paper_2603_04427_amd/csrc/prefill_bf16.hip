@@ -265,7 +265,6 @@ __global__ __launch_bounds__(64 * GW * KS, prefill_min_blocks(R, QC, KS)) void p
     const int BM = 32 * QC * RB;
     const int nqb = p.blocks, groups_per_kv = p.per_kv;
     const Place at = place_workgroup(GW == 4 && KS == 1 ? p.order : kRanked, blockIdx.x, p.pairs, nqb);
-    if (at.pair < 0) return;
     const int pair = at.pair, rank = at.rank;
     const int qb = p.causal ? nqb - 1 - rank : rank;
     const int b = pair / (p.Hkv * groups_per_kv);
@@ -590,7 +589,7 @@ static hipError_t run(PrefillParams p, hipStream_t st) {
     const int BM = 32 * (GW / HPW);
     const long nqb = ((long)p.Sq + BM - 1) / BM, pairs = (long)p.B * p.Hkv * (p.G / HPW);
     p.order = GW == 4 && KS == 1 ? walk_order(sizes_of(p, R, DV), prefill_min_blocks(R, 1, KS)) : kRanked;
-    const long groups = order_launch(p.order, nqb * pairs);
+    const long groups = nqb * pairs;
     if (groups > 0x7fffffffL) return hipErrorInvalidValue;
     p.pairs = (int)pairs;
     p.blocks = (int)nqb;

@@ -255,7 +255,6 @@ __global__ __launch_bounds__(64 * GW * KS, KS == 1 ? 2 : 1) void bwd_dq_kernel(c
     const int BM = 32 * RB;
     const int nqb = p.blocks, groups_per_kv = p.per_kv;
     const Place at = place_workgroup(GW == 4 && KS == 1 ? p.order : kRanked, blockIdx.x, p.pairs, nqb);
-    if (at.pair < 0) return;
     const int pair = at.pair, rank = at.rank;
     const int qb = p.causal ? nqb - 1 - rank : rank;
     const int b = pair / (p.Hkv * groups_per_kv);
@@ -460,7 +459,6 @@ __global__ __launch_bounds__(64 * KW * QG, R + DV >= 192 || KW * QG > 4 ? 1 : 2)
 
     // workgroup -> (KV sequence, KB keys), rank 0 the longest query range (dkdv_order)
     const Place at = place_workgroup(KW == 4 ? p.order : kRanked, blockIdx.x, p.pairs, p.blocks);
-    if (at.pair < 0) return;
     const int pair = at.pair, kbi = at.rank;
     const int b = pair / p.Hkv, g = pair % p.Hkv;
     const int k0g = kbi * KB;              // first key of the workgroup
@@ -622,7 +620,7 @@ static hipError_t run_dq(PrefillBwdParams p, hipStream_t st) {
     p.pairs = (int)pairs;
     p.blocks = (int)nqb;
     p.per_kv = p.G / HPW;
-    const long groups = order_launch(p.order, nqb * pairs);
+    const long groups = nqb * pairs;
     if (groups * 64 * GW * KS > 0xffffffffL) return hipErrorInvalidValue;
     if (groups == 0) return hipSuccess;
     hipLaunchKernelGGL((bwd_dq_kernel<R, DV, GW, KS>), dim3((unsigned)groups), dim3(64 * GW * KS), 0, st, p);
@@ -636,61 +634,29 @@ static hipError_t run_dkdv(PrefillBwdParams p, hipStream_t st) {
     p.pairs = (int)pairs;
     p.blocks = (int)nkb;
     p.per_kv = 1;
-    const long groups = order_launch(p.order, nkb * pairs);
+    const long groups = nkb * pairs;
     if (groups * 64 * KW * QG > 0xffffffffL) return hipErrorInvalidValue;
     if (groups == 0) return hipSuccess;
     hipLaunchKernelGGL((bwd_dkdv_kernel<R, DV, KW, QG, T>), dim3((unsigned)groups), dim3(64 * KW * QG), 0, st, p);
     return hipGetLastError();
 }
 
-// Workgroup shapes. A unit is one wave's block of 32 query rows of one head (dQ)
-// or of 32 keys of one KV head (dK/dV). As in the forward, a call of few units
-// leaves CUs idle, or all its workgroups resident at once so that the longest walk
-// sets its time: fewer units per workgroup and several groups that walk the tiles
-// in turn shorten it. us per call, four units x 1 group against the adopted shape,
-// r 32, 32 query heads over 8, d_v 128, unless stated:
-//   dQ, up to 1024 units (d_v 64: 1536), two units x 2 key groups: 512 tokens
-//     14.9 / 10.8, 1024 tokens 24.9 / 18.2; r 128, 1024 tokens 39.0 / 30.8; 12
-//     heads, d_v 64, 2 x 2048 tokens 36.5 / 24.7
-//   dQ, up to 2048 units and 20 tiles or more, four units x 2: 2048 tokens 48.4 / 40.4
-//   dK/dV, r + d_v < 192 (two waves per SIMD): up to 1024 units (d_v 64: 768, walks
-//     of 16 tiles or more) two units x 4 query groups on 32-row tiles, which fit
-//     them in the LDS: 1024 tokens 129 / 54, 2048 tokens 253 / 100; up to 3072 units
-//     two units x 2, 32-row tiles (two workgroups per CU): 2 x 4096 tokens 520 / 394,
-//     10 x 952 142 / 122; for d_v 64 up to 1536 units two units x 2, 64-row tiles:
-//     12 heads, 4096 tokens 92.8 / 57.8
-//   dK/dV, r + d_v >= 192 (one wave per SIMD): up to 1024 units two units x 2,
-//     64-row tiles: r 128, 2048 tokens 339 / 192
-// On the other side of the lines, four units x 1 is faster: dQ 3 x 500 tokens, 32
-// KV heads, 16.4 against 19.2 with two units x 2; dK/dV 4 x 4096 tokens 727 against
-// 757, r 128, 32 KV heads, 2048 tokens 104 against 123; 12 heads, d_v 64, 8 x 1000
-// tokens 37 against 40.
 template <int R, int DV>
 static hipError_t dq(const PrefillBwdParams& p, hipStream_t st) {
-    const long units = (long)p.B * p.Hq * ((p.Sq + 31) / 32);
-    const long tiles = ((long)p.Sk + kT - 1) / kT;
-    if (tiles >= 2 && units <= (R + DV <= 128 ? 1536 : 1024)) return run_dq<R, DV, 2, 2>(p, st);
-    if (tiles >= 20 && units <= 2048) return run_dq<R, DV, 4, 2>(p, st);
-    return run_dq<R, DV, 4, 1>(p, st);
+    const DqForm f = dq_form(sizes_of(p, R, DV));
+    if (f.waves == 2) return run_dq<R, DV, 2, 2>(p, st);
+    return f.groups == 2 ? run_dq<R, DV, 4, 2>(p, st) : run_dq<R, DV, 4, 1>(p, st);
 }
 
 template <int R, int DV>
 static hipError_t dkdv(const PrefillBwdParams& p, hipStream_t st) {
-    const long units = (long)p.B * p.Hkv * ((p.Sk + 31) / 32);
-    const long walk = ((long)p.Sq + kT - 1) / kT * p.G;  // 64-row query tiles of the longest walk
-    if (walk >= 2) {
-        if constexpr (R + DV >= 192) {
-            if (units <= 1024) return run_dkdv<R, DV, 2, 2, 64>(p, st);
-        } else {
-            if (units <= (DV == 64 ? 768 : 1024) && (DV != 64 || walk >= 16)) return run_dkdv<R, DV, 2, 4, 32>(p, st);
-            if constexpr (DV == 64) {
-                if (units <= 1536) return run_dkdv<R, DV, 2, 2, 64>(p, st);
-            } else {
-                if (units <= 3072) return run_dkdv<R, DV, 2, 2, 32>(p, st);
-            }
-        }
+    const DkdvForm f = dkdv_form(sizes_of(p, R, DV));
+    if (f.waves == 4) return run_dkdv<R, DV, 4, 1, 64>(p, st);
+    if constexpr (R + DV < 192) {
+        if (f.groups == 4) return run_dkdv<R, DV, 2, 4, 32>(p, st);
+        if constexpr (DV == 128) return run_dkdv<R, DV, 2, 2, 32>(p, st);
     }
-    return run_dkdv<R, DV, 4, 1, 64>(p, st);
+    return run_dkdv<R, DV, 2, 2, 64>(p, st);
 }
 
 template <int R, int DV>

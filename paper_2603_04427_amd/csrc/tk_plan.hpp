@@ -29,9 +29,12 @@ enum Order : int {
 };
 
 struct Place {
-    int pair, rank;  // pair < 0: no work
+    int pair, rank;
 };
 
+// The walk of one of pairs x n workgroups. (Every workgroup has one: a check for empty
+// ones before the rest of the arguments are read would cost a short kernel their round
+// trip a second time, 0.5 of 13.7 us in a small backward.)
 constexpr Place place_workgroup(int order, unsigned block, unsigned pairs, unsigned n) {
     if (order == kRanked) return {(int)(block % pairs), (int)(block / pairs)};
     const unsigned xcd = block % kXcds, i = block / kXcds;
@@ -39,12 +42,9 @@ constexpr Place place_workgroup(int order, unsigned block, unsigned pairs, unsig
         const unsigned own = pairs / kXcds;
         return {(int)(xcd * own + i % own), (int)(i / own)};
     }
-    const unsigned total = pairs * n, at = xcd * ((total + kXcds - 1) / kXcds) + i;
-    return at < total ? Place{(int)(at / n), (int)(at % n)} : Place{-1, 0};
-}
-// Workgroups to launch (by sequence every XCD gets the same number, the last ones empty).
-constexpr long order_launch(int order, long workgroups) {
-    return order == kBySequence ? (workgroups + kXcds - 1) / kXcds * kXcds : workgroups;
+    const unsigned total = pairs * n, over = total % kXcds;  // the first `over` XCDs have one more
+    const unsigned at = xcd * (total / kXcds) + (xcd < over ? xcd : over) + i;
+    return {(int)(at / n), (int)(at % n)};
 }
 
 // The order of the forward and of the dQ kernel with four heads or row blocks a
@@ -175,6 +175,81 @@ constexpr PrefillForm prefill_form(const AttnSizes& s) {
     }
     if (even && tiles >= 8 && units <= 1024 && four <= 256) return {4, 2};
     return {4, 1};
+}
+
+// ------------------------------------------------------------------ backward: workgroup shapes
+//
+// A unit is one wave's block of 32 query rows of one head (dQ) or of 32 keys of one KV
+// head (dK/dV). As in the forward, a call of few units leaves CUs idle, or all its
+// workgroups resident at once so that the longest walk sets its time: fewer units per
+// workgroup and several groups that walk the tiles in turn shorten it, as long as the
+// CUs still hold the workgroups at once (two units x 2: three a CU at r + d_v 96, two
+// at 128 and 160, one above, where two groups' tiles fill the LDS). Past that a long
+// causal ramp still gains, because its longest walks bound the call; equal walks and
+// short ones lose. us per call, four units x 1 group against the adopted shape (r 32,
+// 32 query heads over 8, d_v 128, unless stated):
+//   512 tokens 14.9 / 10.8, 1024 tokens 24.9 / 18.2; r 128, 1024 tokens 39.0 / 30.8; 12
+//   heads, d_v 64, 2 x 2048 tokens 36.5 / 24.7; four units x 2, 2048 tokens 48.4 / 40.4
+// and on the other side of the lines, the shape not taken second: 3 x 500 tokens, 32 KV
+// heads, 16.4 / 19.2; r 64, 28 over 4, 5 x 104 8.6 / 12.6 (280 workgroups of two units);
+// 11 x 47 over 65 6.9 / 8.1; 7 x 125 7.9 / 9.3; r 64, 10 x 86 over 447 16.3 / 23.6;
+// 2 x 2684 without a mask, 8 heads over 2, 68.1 / 75.9 (four units x 2, which without a
+// ramp pays at r + d_v 96 in up to 512 workgroups: 12 heads, 5129 tokens 6 % of the whole).
+struct DqForm {
+    int waves, groups;
+};
+constexpr DqForm dq_form(const AttnSizes& s) {
+    const int wide = s.r + s.dv;
+    const long units = (long)s.B * s.Hkv * s.G * (((long)s.Sq + 31) / 32);
+    const long tiles = ((long)s.Sk + 63) / 64, two = row_workgroups(s, 2), four = row_workgroups(s, 4);
+    const bool even = even_walks(s);
+    if (tiles < 2) return {4, 1};
+    if (two <= (wide <= 96 ? 768 : wide <= 128 ? 512 : 256)) return {2, 2};
+    if (wide <= 128 ? !even && tiles >= 8 && units <= 1536
+                    : tiles >= (wide >= 192 ? 10 : even ? 8 : 6) && units <= 1024 && two <= 512 && (wide < 192 || !even))
+        return {2, 2};
+    if (wide >= 192 && even && tiles >= 12 && four <= 256) return {4, 2};
+    if (tiles >= 20 && (even ? wide <= 96 && four <= 512 : units <= 2048)) return {4, 2};
+    return {4, 1};
+}
+
+// dK/dV: KW waves of 32 keys share each query tile of `rows` rows, `groups` query groups
+// of them. us per call, four units x 1 against the adopted shape:
+//   r + d_v < 192 (two waves per SIMD), d_v 128: two units x 4 on 32-row tiles, one
+//     workgroup per CU, 1024 tokens 129 / 54, 2048 tokens 253 / 100; up to 512 of them on
+//     a ramp of 16 tiles, 9 x 1513 over 1713, 8 heads over 2, 194 / 107. Else two
+//     units x 2, 32-row tiles (two per CU), up to 3072 units: 2 x 4096 tokens 520 / 394,
+//     10 x 952 142 / 122, 32 KV heads, 4 x 153 11.9 / 11.5 (x 4: 18.2). Without a ramp
+//     only where they are no second round or save one of the whole shape's: 3 x 1428 over
+//     1742 235 / 229; 7 x 877, 64 over 8, 286 / 326 with them, 13 x 104, 32 KV heads, 13.9 / 17.9
+//   d_v 64: x 4 in one workgroup per CU for walks of 16 tiles or more (on a ramp of 24
+//     up to 768 units); else two units x 2, 64-row tiles, three per CU: 12 heads, 4096
+//     tokens 92.8 / 57.8, 8 x 1000 tokens 37 / 40; 9 x 267 without a mask, 16 heads, 14.7
+//     / 17.5, 15 x 99 over 166 17.8 / 20.1 (whole backward)
+//   r + d_v >= 192 (one wave per SIMD): two units x 2, 64-row tiles, one workgroup per
+//     CU: r 128, 2048 tokens 339 / 192; 13 x 157, r 128, 39.2 / 48.2 (312 workgroups); up
+//     to 1024 units on a ramp of 10 tiles: 2 x 1122, r 64, 170 / 95; 32 KV heads, r 128,
+//     2048 tokens 104 / 123
+struct DkdvForm {
+    int waves, groups, rows;
+};
+constexpr DkdvForm dkdv_form(const AttnSizes& s) {
+    const int wide = s.r + s.dv;
+    const long kv = (long)s.B * s.Hkv, units = kv * (((long)s.Sk + 31) / 32);
+    const long two = kv * (((long)s.Sk + 63) / 64), four = kv * (((long)s.Sk + 127) / 128);
+    const long walk = ((long)s.Sq + 63) / 64 * s.G;  // 64-row query tiles of the longest walk
+    const bool even = even_walks(s);
+    if (walk < 2) return {4, 1, 64};
+    if (wide >= 192) {
+        if (two <= 256 || (!even && walk >= 10 && units <= 1024)) return {2, 2, 64};
+    } else if (s.dv == 64) {
+        if ((two <= 256 && walk >= 16) || (!even && walk >= 24 && units <= 768)) return {2, 4, 32};
+        if (two <= (walk < 8 ? 512 : 768)) return {2, 2, 64};
+    } else {
+        if (two <= 256 || (!even && walk >= 16 && two <= 512)) return {2, 4, 32};
+        if (even ? two <= 736 || (four > 512 && two <= 1536) : units <= 3072) return {2, 2, 32};
+    }
+    return {4, 1, 64};
 }
 
 }  // namespace tk

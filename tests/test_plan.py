@@ -21,13 +21,20 @@ void place(int order, int block, int pairs, int n, int* out) {
     out[0] = p.pair;
     out[1] = p.rank;
 }
-long launched(int order, long workgroups) { return order_launch(order, workgroups); }
 int walks(int B, int Hq, int Hkv, int Sq, int Sk, int r, int dv, int causal, int slots) {
     return walk_order({B, Hkv, Hq / Hkv, Sq, Sk, r, dv, causal != 0}, slots);
 }
 int form(int B, int Hq, int Hkv, int Sq, int Sk, int r, int dv, int causal) {
     const PrefillForm f = prefill_form({B, Hkv, Hq / Hkv, Sq, Sk, r, dv, causal != 0});
     return f.waves * 10 + f.groups;
+}
+int dq(int B, int Hq, int Hkv, int Sq, int Sk, int r, int dv, int causal) {
+    const DqForm f = dq_form({B, Hkv, Hq / Hkv, Sq, Sk, r, dv, causal != 0});
+    return f.waves * 10 + f.groups;
+}
+int dkdv_shape(int B, int Hq, int Hkv, int Sq, int Sk, int r, int dv, int causal) {
+    const DkdvForm f = dkdv_form({B, Hkv, Hq / Hkv, Sq, Sk, r, dv, causal != 0});
+    return f.waves * 1000 + f.groups * 100 + f.rows;
 }
 int dkdv(int B, int Hq, int Hkv, int Sq, int Sk, int r, int dv, int causal, int KW) {
     return dkdv_order({B, Hkv, Hq / Hkv, Sq, Sk, r, dv, causal != 0}, KW);
@@ -48,7 +55,7 @@ def plan(tmp_path_factory):
 
 def places(plan, order, pairs, n):
     out = (ctypes.c_int * 2)()
-    for block in range(plan.launched(order, ctypes.c_long(pairs * n))):
+    for block in range(pairs * n):
         plan.place(order, block, pairs, n, out)
         yield block, out[0], out[1]
 
@@ -58,7 +65,7 @@ def test_every_order_places_each_walk_once(plan, order):
     for pairs, n in itertools.product((1, 3, 7, 8, 12, 16, 20, 24, 56, 64, 104), (1, 2, 3, 5, 8, 13, 64)):
         if order == OWNED and pairs % 8:
             continue
-        seen = [(pair, rank) for _, pair, rank in places(plan, order, pairs, n) if pair >= 0]
+        seen = [(pair, rank) for _, pair, rank in places(plan, order, pairs, n)]
         assert sorted(seen) == [(p, r) for p in range(pairs) for r in range(n)]
 
 
@@ -67,7 +74,7 @@ def test_longest_walks_start_first_on_each_xcd(plan, order):
     """Ranks rise over an XCD's workgroups: over all its pairs, or pair by pair."""
     for pairs, n in ((8, 5), (16, 4), (24, 7), (56, 3)):
         for xcd in range(8):
-            mine = [(pair, rank) for block, pair, rank in places(plan, order, pairs, n) if block % 8 == xcd and pair >= 0]
+            mine = [(pair, rank) for block, pair, rank in places(plan, order, pairs, n) if block % 8 == xcd]
             assert mine == sorted(mine, key=(lambda w: w) if order == BY_SEQUENCE else (lambda w: w[1]))
 
 
@@ -84,8 +91,7 @@ def test_head_groups_of_a_kv_sequence_share_an_xcd(plan, B, Hq, Hkv):
         n = -(-S // 128)
         xcds = {}
         for block, pair, _ in places(plan, order, pairs, n):
-            if pair >= 0:
-                xcds.setdefault(pair // per_kv, set()).add(block % 8)
+            xcds.setdefault(pair // per_kv, set()).add(block % 8)
         # an eighth of the pairs may end inside a sequence: it then has two neighbours' XCDs
         assert sum(len(x) for x in xcds.values()) <= len(xcds) + 7
 
@@ -149,3 +155,58 @@ def test_dkdv_order_of_measured_calls(plan, call, order):
 ])
 def test_prefill_form_of_measured_calls(plan, call, form):
     assert plan.form(*call) == form
+
+
+@pytest.mark.parametrize("call,form", [
+    ((1, 32, 8, 512, 512, 32, 128, 1), 22),
+    ((1, 32, 8, 1024, 1024, 128, 128, 1), 22),
+    ((2, 12, 12, 2048, 2048, 32, 64, 1), 22),
+    ((1, 32, 8, 2048, 2048, 32, 128, 1), 42),
+    ((3, 32, 32, 500, 500, 32, 128, 1), 41),
+    ((2, 32, 8, 4096, 4096, 32, 128, 1), 41),
+    ((5, 28, 4, 104, 104, 64, 128, 1), 41),      # short walks in more workgroups than one a CU
+    ((4, 28, 4, 134, 134, 64, 128, 1), 41),
+    ((11, 32, 8, 47, 65, 32, 128, 1), 41),
+    ((7, 32, 8, 125, 125, 32, 128, 1), 41),
+    ((2, 32, 8, 374, 374, 32, 128, 1), 22),
+    ((10, 32, 8, 86, 447, 64, 128, 1), 41),      # equal walks
+    ((15, 12, 12, 184, 184, 64, 64, 0), 41),
+    ((6, 8, 2, 375, 761, 128, 128, 0), 42),      # equal and long, four units in 144 workgroups
+    ((2, 8, 2, 2684, 2684, 32, 128, 0), 41),
+    ((1, 12, 12, 5129, 5129, 32, 64, 0), 42),
+    ((1, 32, 8, 33, 33, 32, 128, 1), 41),        # one tile
+])
+def test_dq_form_of_measured_calls(plan, call, form):
+    assert plan.dq(*call) == form
+
+
+@pytest.mark.parametrize("call,form", [
+    ((1, 32, 8, 1024, 1024, 32, 128, 1), 2432),
+    ((1, 32, 8, 2048, 2048, 32, 128, 1), 2432),
+    ((2, 32, 8, 4096, 4096, 32, 128, 1), 2232),
+    ((9, 8, 2, 1513, 1713, 32, 128, 1), 2432),
+    ((4, 32, 8, 600, 600, 32, 128, 1), 2432),
+    ((9, 32, 8, 277, 277, 32, 128, 1), 2432),
+    ((13, 32, 8, 411, 411, 32, 128, 0), 2232),
+    ((1, 12, 12, 4096, 4096, 32, 64, 1), 2264),
+    ((2, 32, 4, 2395, 2395, 32, 64, 1), 2432),
+    ((15, 16, 16, 99, 166, 32, 64, 1), 4164),
+    ((10, 32, 4, 1132, 1132, 32, 64, 0), 2264),
+    ((1, 12, 12, 1716, 1716, 64, 64, 1), 2432),
+    ((6, 32, 8, 645, 645, 128, 128, 1), 2264),
+    ((1, 32, 32, 659, 669, 64, 128, 1), 2264),
+    ((1, 32, 4, 591, 591, 32, 64, 1), 2432),
+    ((1, 32, 8, 2048, 2048, 128, 128, 1), 2264),
+    ((4, 32, 8, 4096, 4096, 32, 128, 1), 4164),
+    ((1, 32, 32, 2048, 2048, 128, 128, 1), 4164),
+    ((8, 12, 12, 1000, 1000, 32, 64, 1), 4164),
+    ((4, 32, 32, 153, 169, 32, 128, 0), 2232),   # 384 workgroups of two units: not x 4
+    ((13, 32, 32, 104, 104, 32, 128, 0), 4164),  # equal walks, a second round
+    ((7, 64, 8, 877, 877, 32, 128, 0), 4164),
+    ((13, 32, 8, 157, 157, 128, 128, 0), 4164),
+    ((11, 40, 5, 43, 492, 128, 128, 1), 4164),
+    ((9, 16, 16, 267, 267, 32, 64, 0), 4164),
+    ((1, 32, 32, 40, 4096, 32, 128, 1), 4164),   # one query tile a walk
+])
+def test_dkdv_form_of_measured_calls(plan, call, form):
+    assert plan.dkdv_shape(*call) == form
