@@ -228,7 +228,8 @@ constexpr DqForm dq_form(const AttnSizes& s) {
 //     / 17.5, 15 x 99 over 166 17.8 / 20.1 (whole backward)
 //   r + d_v >= 192 (one wave per SIMD): two units x 2, 64-row tiles, one workgroup per
 //     CU: r 128, 2048 tokens 339 / 192; 13 x 157, r 128, 39.2 / 48.2 (312 workgroups); up
-//     to 1024 units on a ramp of 10 tiles: 2 x 1122, r 64, 170 / 95; 32 KV heads, r 128,
+//     to 1024 units on a ramp of 8 tiles: 2 x 1122, r 64, 170 / 95, 32 KV heads, 512 over 518
+//     53 / 42 (whole backward); 32 KV heads, r 128,
 //     2048 tokens 104 / 123
 struct DkdvForm {
     int waves, groups, rows;
@@ -241,7 +242,7 @@ constexpr DkdvForm dkdv_form(const AttnSizes& s) {
     const bool even = even_walks(s);
     if (walk < 2) return {4, 1, 64};
     if (wide >= 192) {
-        if (two <= 256 || (!even && walk >= 10 && units <= 1024)) return {2, 2, 64};
+        if (two <= 256 || (!even && walk >= 8 && units <= 1024)) return {2, 2, 64};
     } else if (s.dv == 64) {
         if ((two <= 256 && walk >= 16) || (!even && walk >= 24 && units <= 768)) return {2, 4, 32};
         if (two <= (walk < 8 ? 512 : 768)) return {2, 2, 64};

@@ -195,6 +195,7 @@ def test_dq_form_of_measured_calls(plan, call, form):
     ((1, 12, 12, 1716, 1716, 64, 64, 1), 2432),
     ((6, 32, 8, 645, 645, 128, 128, 1), 2264),
     ((1, 32, 32, 659, 669, 64, 128, 1), 2264),
+    ((1, 32, 32, 512, 518, 64, 128, 1), 2264),
     ((1, 32, 4, 591, 591, 32, 64, 1), 2432),
     ((1, 32, 8, 2048, 2048, 128, 128, 1), 2264),
     ((4, 32, 8, 4096, 4096, 32, 128, 1), 4164),
