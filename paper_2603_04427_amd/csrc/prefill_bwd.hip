@@ -613,44 +613,37 @@ static AttnSizes sizes_of(const PrefillBwdParams& p, int R, int DV) {
 
 template <int R, int DV, int GW, int KS>
 static hipError_t run_dq(PrefillBwdParams p, hipStream_t st) {
-    const int HPW = heads_per_group(p.G, GW);
-    const int BM = 32 * (GW / HPW);
-    const long nqb = ((long)p.Sq + BM - 1) / BM, pairs = (long)p.B * p.Hkv * (p.G / HPW);
-    p.order = GW == 4 && KS == 1 ? walk_order(sizes_of(p, R, DV), 2) : kRanked;
-    p.pairs = (int)pairs;
-    p.blocks = (int)nqb;
-    p.per_kv = p.G / HPW;
-    const long groups = nqb * pairs;
-    if (groups * 64 * GW * KS > 0xffffffffL) return hipErrorInvalidValue;
+    const AttnSizes s = sizes_of(p, R, DV);
+    const long groups = row_workgroups(s, GW);
     if (groups == 0) return hipSuccess;
+    p.order = GW == 4 && KS == 1 ? walk_order(s, 2) : kRanked;
+    p.per_kv = p.G / heads_per_group(p.G, GW);
+    p.pairs = p.B * p.Hkv * p.per_kv;
+    p.blocks = (int)(groups / p.pairs);
     hipLaunchKernelGGL((bwd_dq_kernel<R, DV, GW, KS>), dim3((unsigned)groups), dim3(64 * GW * KS), 0, st, p);
     return hipGetLastError();
 }
 
 template <int R, int DV, int KW, int QG, int T>
 static hipError_t run_dkdv(PrefillBwdParams p, hipStream_t st) {
-    const long nkb = ((long)p.Sk + 32 * KW - 1) / (32 * KW), pairs = (long)p.B * p.Hkv;
-    p.order = dkdv_order(sizes_of(p, R, DV), KW);
-    p.pairs = (int)pairs;
-    p.blocks = (int)nkb;
+    const AttnSizes s = sizes_of(p, R, DV);
+    const long groups = key_workgroups(s, KW);
+    p.order = dkdv_order(s, KW);
     p.per_kv = 1;
-    const long groups = nkb * pairs;
-    if (groups * 64 * KW * QG > 0xffffffffL) return hipErrorInvalidValue;
-    if (groups == 0) return hipSuccess;
+    p.pairs = p.B * p.Hkv;
+    p.blocks = (int)(groups / p.pairs);
     hipLaunchKernelGGL((bwd_dkdv_kernel<R, DV, KW, QG, T>), dim3((unsigned)groups), dim3(64 * KW * QG), 0, st, p);
     return hipGetLastError();
 }
 
 template <int R, int DV>
-static hipError_t dq(const PrefillBwdParams& p, hipStream_t st) {
-    const DqForm f = dq_form(sizes_of(p, R, DV));
+static hipError_t dq(const PrefillBwdParams& p, const DqForm& f, hipStream_t st) {
     if (f.waves == 2) return run_dq<R, DV, 2, 2>(p, st);
     return f.groups == 2 ? run_dq<R, DV, 4, 2>(p, st) : run_dq<R, DV, 4, 1>(p, st);
 }
 
 template <int R, int DV>
-static hipError_t dkdv(const PrefillBwdParams& p, hipStream_t st) {
-    const DkdvForm f = dkdv_form(sizes_of(p, R, DV));
+static hipError_t dkdv(const PrefillBwdParams& p, const DkdvForm& f, hipStream_t st) {
     if (f.waves == 4) return run_dkdv<R, DV, 4, 1, 64>(p, st);
     if constexpr (R + DV < 192) {
         if (f.groups == 4) return run_dkdv<R, DV, 2, 4, 32>(p, st);
@@ -661,8 +654,15 @@ static hipError_t dkdv(const PrefillBwdParams& p, hipStream_t st) {
 
 template <int R, int DV>
 static hipError_t run(const PrefillBwdParams& p, hipStream_t st) {
-    const hipError_t e = dq<R, DV>(p, st);
-    return e == hipSuccess ? dkdv<R, DV>(p, st) : e;
+    const AttnSizes s = sizes_of(p, R, DV);
+    const DqForm q = dq_form(s);
+    const DkdvForm k = dkdv_form(s);
+    // both grids, before the first kernel writes anything
+    if (!launchable(row_workgroups(s, q.waves), q.waves * q.groups) ||
+        !launchable(key_workgroups(s, k.waves), k.waves * k.groups))
+        return hipErrorInvalidValue;
+    const hipError_t e = dq<R, DV>(p, q, st);
+    return e == hipSuccess ? dkdv<R, DV>(p, k, st) : e;
 }
 
 template <int R>

@@ -121,6 +121,12 @@ constexpr long row_workgroups(const AttnSizes& s, int GW) {
     const int heads = heads_per_group(s.G, GW), rows = 32 * (GW / heads);
     return (long)s.B * s.Hkv * (s.G / heads) * (((long)s.Sq + rows - 1) / rows);
 }
+// Workgroups of KW blocks of 32 keys.
+constexpr long key_workgroups(const AttnSizes& s, int KW) {
+    return (long)s.B * s.Hkv * (((long)s.Sk + 32 * KW - 1) / (32 * KW));
+}
+// Whether one launch takes them (threads in 32 bits).
+constexpr bool launchable(long workgroups, int waves) { return workgroups * 64 * waves <= 0xffffffffL; }
 // LDS of one key group's two K and V tiles, and the most key groups in one CU's LDS (up to 4).
 constexpr int prefill_tile_lds(int r, int dv) { return 2 * 64 * (r + dv) * 2; }
 constexpr int prefill_most_groups(int r, int dv) {
@@ -228,16 +234,14 @@ constexpr DqForm dq_form(const AttnSizes& s) {
 //     / 17.5, 15 x 99 over 166 17.8 / 20.1 (whole backward)
 //   r + d_v >= 192 (one wave per SIMD): two units x 2, 64-row tiles, one workgroup per
 //     CU: r 128, 2048 tokens 339 / 192; 13 x 157, r 128, 39.2 / 48.2 (312 workgroups); up
-//     to 1024 units on a ramp of 8 tiles: 2 x 1122, r 64, 170 / 95, 32 KV heads, 512 over 518
-//     53 / 42 (whole backward); 32 KV heads, r 128,
-//     2048 tokens 104 / 123
+//     to 1024 units on a ramp of 8 tiles: 2 x 1122, r 64, 170 / 95, 32 KV heads, 512
+//     over 518 53 / 42 (whole backward); r 128, 2048 tokens 104 / 123
 struct DkdvForm {
     int waves, groups, rows;
 };
 constexpr DkdvForm dkdv_form(const AttnSizes& s) {
     const int wide = s.r + s.dv;
-    const long kv = (long)s.B * s.Hkv, units = kv * (((long)s.Sk + 31) / 32);
-    const long two = kv * (((long)s.Sk + 63) / 64), four = kv * (((long)s.Sk + 127) / 128);
+    const long units = key_workgroups(s, 1), two = key_workgroups(s, 2), four = key_workgroups(s, 4);
     const long walk = ((long)s.Sq + 63) / 64 * s.G;  // 64-row query tiles of the longest walk
     const bool even = even_walks(s);
     if (walk < 2) return {4, 1, 64};

@@ -279,3 +279,11 @@ def test_bound_calls_convert_arguments_as_ctypes_does():
         call.bind("tk_project_heads", good[:3] + ("2",) + good[4:])
     with pytest.raises(ValueError):
         call.bind("tk_version", ())
+
+
+def test_backward_refuses_before_it_launches_anything():
+    """A call whose dK/dV grid is too large is refused before its dQ kernel could write:
+    2^20 sequences of 9 heads and 129 keys have 18.9 M key blocks, over the 2^24 of 256
+    threads that one launch takes, and 9.4 M row blocks, which would fit."""
+    big = dict(batch=1 << 20, H_q=9, H_kv=9, seq_q=1, seq_k=129, ws_bytes=1 << 40)
+    assert backward(**big) == tb.TK_ERR_UNSUPPORTED
