@@ -173,7 +173,7 @@ size_t tk_attn_decode_workspace_bytes(int batch, int H_q, int H_kv, int max_ctx,
  *       counters zero again, so it can be reused without clearing. Calls that
  *       share one workspace must not run concurrently.
  * Supported: r in {16, 32, 64, 128}; d_v in {64, 128}; H_q % H_kv == 0.
- * The split of the context depends only on the shapes and ctx_lens, so results are bitwise
+ * The split of the context depends only on the shapes, so results are bitwise
  * reproducible from run to run.
  */
 tk_status tk_attn_decode(const void* Q, const void* K_cache, const void* V_cache, void* O,

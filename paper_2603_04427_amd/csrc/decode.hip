@@ -133,11 +133,6 @@ struct DecodeSchedule {
     static constexpr bool kShort = !kFits64 && 64 / LPT <= 32;
     static constexpr int CH = kShort ? 32 : 64;
     static constexpr bool PIPE = kFits64 || kBase + kRegs64 + HG * LPT <= 200;
-    // Whether splits are dealt by length (deal_split). Not with eight heads a
-    // workgroup, whose arithmetic bounds it (16 unequal sequences, 64 heads over 8, r
-    // 16, fp8 keys: 30.4 us before, 31.8 with dealing), nor at 4-bit keys of r 16 and
-    // d_v 128, whose 64-token chunks fill the registers (dealing made them spill).
-    static constexpr bool kDeals = HG < 8 && kBase + (PIPE ? 2 : 1) * (kRegs64 * CH / 64) + HG * LPT <= 240;
 };
 
 // One chunk of CH tokens as this lane holds it.
@@ -366,111 +361,6 @@ __device__ __forceinline__ void process_chunk(Chunk<R, DV, HG, KF, CH>& c, int n
     wave_lds_sync();
 }
 
-// ------------------------------------------------------------------ dealing splits to sequences
-//
-// The grid has n_split workgroups per (sequence, head group). Where the lengths
-// differ, equal split counts make the longest sequence's workgroups walk far more
-// rounds than the mean, and the step ends with most of the chip idle. So the
-// splits are dealt by length: with l the smallest number of rounds per split for
-// which sum over b of ceil(rounds_b / l) <= B n_split, sequence b gets
-// n_b = ceil(rounds_b / l) of them. Workgroup (b, s) keeps split s of its own
-// sequence while s < n_b (so the chunk it requested before it knew any length
-// still counts); the others take, in grid order, the splits from n_split on that
-// longer sequences are owed, or exit. The partials of a sequence lie together, the
-// sequences one after the other. Every wave works this out for itself, one
-// sequence a lane; the result depends on the lengths and shapes alone.
-//
-// Equal lengths skip it all, and l stays at least kMinSplitTokens (shorter splits
-// cost more in the merge than they win). The eight-wave kernels, whose splits are
-// about that short, have none of it (it cost them 0.3 of 10.0 us in code alone).
-// Measured with 32 heads over 8, r 32, d_v 128, lengths spread from an eighth of the
-// longest to all of it: 16 sequences up to 4096 tokens 25.9 -> 22.6 us, 24 up to 3000
-// (fp8 keys) 25.9 -> 21.7, 4 up to 16384 (fp8 keys) 26.7 -> 23.8; equal lengths the same.
-constexpr int kDealSequences = 64;
-constexpr int kMinSplitTokens = 512;
-
-// n / d for n < 2^22 and d >= 1: the quotient of n + 1/2 lies at least 1 / (2 d)
-// from an integer, more than the error of the reciprocal and the product.
-__device__ __forceinline__ unsigned div_small(unsigned n, float rcp_d) {
-    return (unsigned)(((float)n + 0.5f) * rcp_d);
-}
-template <int CTRL, int ROWS = 0xF>
-__device__ __forceinline__ unsigned dpp_u32(unsigned x) {
-    return (unsigned)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, ROWS, 0xF, false);
-}
-// Sum over lanes 0 .. lane (row shifts inside each row of 16 lanes, then the row
-// ends broadcast to the rows behind them).
-__device__ __forceinline__ unsigned wave_scan(unsigned x) {
-    x += dpp_u32<0x111>(x);
-    x += dpp_u32<0x112>(x);
-    x += dpp_u32<0x114>(x);
-    x += dpp_u32<0x118>(x);
-    x += dpp_u32<0x142, 0xA>(x);
-    x += dpp_u32<0x143, 0xC>(x);
-    return x;
-}
-__device__ __forceinline__ unsigned lane63(unsigned x) { return (unsigned)__builtin_amdgcn_readlane((int)x, 63); }
-
-struct Deal {
-    int b, split;  // this workgroup's sequence and split (b < 0: none is left for it)
-    int n, first;  // splits of the sequence, and the place of the first one's partial
-};
-
-// len: the clamped length of sequence `lane` (0 past the last). UNIT: tokens of a
-// round.
-template <int UNIT>
-__device__ __forceinline__ Deal deal_split(int len, int B, int n_split, int b, int split, int lane) {
-    Deal d = {b, split, n_split, b * n_split};
-    const bool mine = lane < B;
-    const int len0 = __builtin_amdgcn_readfirstlane(len);
-    if (__builtin_amdgcn_ballot_w64(mine && len != len0) == 0) return d;
-    const unsigned rounds = mine ? (len > 0 ? ((unsigned)len + UNIT - 1) / UNIT : 1u) : 0u;  // empty: written too
-    const unsigned slots = (unsigned)(B * n_split);
-    const float rcp_n = __builtin_amdgcn_rcpf((float)n_split);
-    unsigned hi = 0;  // rounds per split of equal counts, which always fit
-    {
-        unsigned m = rounds;
-        auto mx = [](unsigned x, unsigned y) { return x > y ? x : y; };
-        m = mx(m, dpp_u32<0x111>(m));
-        m = mx(m, dpp_u32<0x112>(m));
-        m = mx(m, dpp_u32<0x114>(m));
-        m = mx(m, dpp_u32<0x118>(m));
-        m = mx(m, dpp_u32<0x142, 0xA>(m));
-        m = mx(m, dpp_u32<0x143, 0xC>(m));
-        hi = div_small(lane63(m) + n_split - 1, rcp_n);
-    }
-    unsigned lo = div_small(lane63(wave_scan(rounds)) + slots - 1, __builtin_amdgcn_rcpf((float)slots));
-    const unsigned least = kMinSplitTokens / UNIT > 0 ? kMinSplitTokens / UNIT : 1;
-    lo = lo > least ? lo : least;
-    if (lo >= hi) return d;
-    while (lo < hi) {
-        const unsigned mid = (lo + hi) / 2;
-        const unsigned cnt = div_small(rounds + mid - 1, __builtin_amdgcn_rcpf((float)mid));
-        if (lane63(wave_scan(cnt)) <= slots)
-            hi = mid;
-        else
-            lo = mid + 1;
-    }
-    const unsigned n = div_small(rounds + hi - 1, __builtin_amdgcn_rcpf((float)hi));
-    const unsigned owed = n > (unsigned)n_split ? n - n_split : 0;          // splits past the sequence's own slots
-    const unsigned free_slots = mine && n < (unsigned)n_split ? n_split - n : 0;
-    const unsigned owed_at = wave_scan(owed) - owed, free_at = wave_scan(free_slots) - free_slots;
-    const unsigned my_n = (unsigned)__builtin_amdgcn_readlane((int)n, b);
-    if ((unsigned)split >= my_n) {
-        const unsigned k = (unsigned)__builtin_amdgcn_readlane((int)free_at, b) + split - my_n;
-        const uint64_t hit = __builtin_amdgcn_ballot_w64(k >= owed_at && k < owed_at + owed);
-        if (hit == 0) {
-            d.b = -1;
-            return d;
-        }
-        d.b = __builtin_ctzll(hit);
-        d.split = n_split + (int)(k - (unsigned)__builtin_amdgcn_readlane((int)owed_at, d.b));
-    }
-    d.n = __builtin_amdgcn_readlane((int)n, d.b);
-    d.first = __builtin_amdgcn_readlane((int)(wave_scan(n) - n), d.b);
-    return d;
-}
-
 // Two four-wave workgroups per CU where the registers allow it; 4-bit keys with
 // eight heads per workgroup (their unpacked query slices are twice as wide), and
 // every eight-wave form, take the whole register file of one.
@@ -497,53 +387,37 @@ __global__ __launch_bounds__(64 * NW, (decode_min_blocks<HG, KF, NW>())) void de
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    int split = blockIdx.x;
+    const int split = blockIdx.x;
     const int groups_per_kv = p.G / HG;
     const int g = blockIdx.y / groups_per_kv;
     const int h0 = g * p.G + (blockIdx.y % groups_per_kv) * HG;
-    int b = blockIdx.z;
-    int n_split = p.n_split;
-    int first_part = b * n_split;  // the first of this sequence's partials
-
-    constexpr bool DEALS = NW == kDecodeWavesLong && DecodeSchedule<R, DV, HG, KF>::kDeals;
-    const bool deal = DEALS && p.deal != 0;
-    int len = 0;  // sequence `lane`'s length, requested first: all else waits behind the cache stream
-    if (deal) {
-        if (lane < p.B) len = p.ctx_lens[lane];
-        asm volatile("" ::: "memory");
-    }
+    const int b = blockIdx.z;
 
     // this lane's query slice as packed bf16 pairs (exact; the scale is applied in fp32)
     uint32_t qp[HG][S::QW];
     const int kpart = lane % LPT;
-    auto load_queries = [&](int seq) {
 #pragma unroll
-        for (int h = 0; h < HG; ++h) {
-            const uint4* qrow = (const uint4*)(p.q + ((size_t)seq * p.Hq + h0 + h) * R + kpart * S::EPL);
+    for (int h = 0; h < HG; ++h) {
+        const uint4* qrow = (const uint4*)(p.q + ((size_t)b * p.Hq + h0 + h) * R + kpart * S::EPL);
 #pragma unroll
-            for (int i = 0; i < S::QW / 4; ++i) {
-                const uint4 w = qrow[i];
-                qp[h][4 * i] = w.x;
-                qp[h][4 * i + 1] = w.y;
-                qp[h][4 * i + 2] = w.z;
-                qp[h][4 * i + 3] = w.w;
-            }
+        for (int i = 0; i < S::QW / 4; ++i) {
+            const uint4 w = qrow[i];
+            qp[h][4 * i] = w.x;
+            qp[h][4 * i + 1] = w.y;
+            qp[h][4 * i + 2] = w.z;
+            qp[h][4 * i + 3] = w.w;
         }
-    };
-    load_queries(b);
+    }
     // 4-bit keys: sum of this lane's query slice per head
     float qsum[HG];
-    auto sum_queries = [&] {
 #pragma unroll
-        for (int h = 0; h < HG; ++h) {
-            qsum[h] = 0.f;
-            if constexpr (KF == kKeyInt4) {
+    for (int h = 0; h < HG; ++h) {
+        qsum[h] = 0.f;
+        if constexpr (KF == kKeyInt4) {
 #pragma unroll
-                for (int i = 0; i < S::QW; ++i) qsum[h] += bf16lo(qp[h][i]) + bf16hi(qp[h][i]);
-            }
+            for (int i = 0; i < S::QW; ++i) qsum[h] += bf16lo(qp[h][i]) + bf16hi(qp[h][i]);
         }
-    };
-    sum_queries();
+    }
 
     LaneState<HG, NH> st;
 #pragma unroll
@@ -558,15 +432,15 @@ __global__ __launch_bounds__(64 * NW, (decode_min_blocks<HG, KF, NW>())) void de
     bool bad_block = false;
     uint16_t* p16 = (uint16_t*)p_lds[wave];
 
-    // Chunks ts, ts + stride, ... of this wave: a round is kDecodeWaves chunks,
+    // Chunks ts, ts + kStride, ... of this wave: a round is kDecodeWaves chunks,
     // one per wave, and split s takes rounds s, s + n_split, ... With PIPE the
     // next chunk's loads are issued before the current one is processed. For a
     // contiguous cache the first chunk is requested before the context length
     // is read (rows up to max_ctx are readable), so the length's round trip
     // overlaps the stream; paged caches wait for it, because table entries past
-    // the context need not be valid. A workgroup that is dealt another split than
-    // its place in the grid requests that one's first chunk anew.
+    // the context need not be valid.
     using C = Chunk<R, DV, HG, KF, CH>;
+    const int kStride = p.n_split * kDecodeWaves * CH;
     int ts = (split * kDecodeWaves + wave) * CH;
     int first_avail = p.max_ctx;
     C ca;
@@ -577,30 +451,11 @@ __global__ __launch_bounds__(64 * NW, (decode_min_blocks<HG, KF, NW>())) void de
     }
     int L = load_uniform(p.ctx_lens + b);
     L = L < 0 ? 0 : (L > p.max_ctx ? p.max_ctx : L);
+    const int split_end = L;  // every split walks to the end of the context
     if constexpr (PAGED) {
-        first_avail = L;
+        first_avail = split_end;
         if (ts < first_avail) ok_a = load_chunk<R, DV, HG, KF, CH, PAGED>(ca, p, b, g, ts, first_avail, lane);
     }
-    if (deal) {
-        len = len < 0 ? 0 : (len > p.max_ctx ? p.max_ctx : len);
-        const Deal d = deal_split<kDecodeWaves * CH>(len, p.B, n_split, b, split, lane);
-        if (d.b < 0) return;  // the whole workgroup
-        n_split = __builtin_amdgcn_readfirstlane(d.n);
-        first_part = __builtin_amdgcn_readfirstlane(d.first);
-        if (d.b != b) {
-            b = __builtin_amdgcn_readfirstlane(d.b);
-            split = __builtin_amdgcn_readfirstlane(d.split);
-            L = __builtin_amdgcn_readlane(len, b);
-            load_queries(b);
-            sum_queries();
-            ts = (split * kDecodeWaves + wave) * CH;
-            first_avail = L;
-            ok_a = true;
-            if (ts < first_avail) ok_a = load_chunk<R, DV, HG, KF, CH, PAGED>(ca, p, b, g, ts, first_avail, lane);
-        }
-    }
-    const int split_end = L;  // every split walks to the end of the context
-    const int kStride = n_split * kDecodeWaves * CH;
     if (ts < first_avail) {
         if constexpr (PIPE) {
             C cb;
@@ -663,7 +518,6 @@ __global__ __launch_bounds__(64 * NW, (decode_min_blocks<HG, KF, NW>())) void de
     // single split that is the answer: normalise and write the bf16 rows directly.
     constexpr int kOut = (HG * DV + kDecodeThreads - 1) / kDecodeThreads;
     const int ws_row = DV + 2;
-    const size_t part0 = (size_t)blockIdx.y * p.B * p.n_split + first_part;  // partials of a head group lie together
     float M[kOut], O[kOut], Lsum[kOut];
     bool bad[kOut];
 #pragma unroll
@@ -693,7 +547,7 @@ __global__ __launch_bounds__(64 * NW, (decode_min_blocks<HG, KF, NW>())) void de
             bad[u] |= __builtin_isnan(lw[w]);
         }
     }
-    if (n_split == 1) {
+    if (p.n_split == 1) {
 #pragma unroll
         for (int u = 0; u < kOut; ++u) {
             const int idx = threadIdx.x + u * kDecodeThreads;
@@ -712,7 +566,7 @@ __global__ __launch_bounds__(64 * NW, (decode_min_blocks<HG, KF, NW>())) void de
         const int idx = threadIdx.x + u * kDecodeThreads;
         if (idx >= HG * DV) continue;
         const int h = idx / DV, c = idx % DV;
-        float* dst = p.ws + ((part0 + split) * HG + h) * ws_row;
+        float* dst = p.ws + (((size_t)b * p.Hq + h0 + h) * p.n_split + split) * ws_row;
         store_coherent(dst + c, O[u]);
         if (c == 0) {
             store_coherent(dst + DV, M[u]);
@@ -728,7 +582,7 @@ __global__ __launch_bounds__(64 * NW, (decode_min_blocks<HG, KF, NW>())) void de
     unsigned* counter = p.counters + (size_t)b * gridDim.y + blockIdx.y;
     if (threadIdx.x == 0)
         is_last = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-                  (unsigned)(n_split - 1);
+                  (unsigned)(p.n_split - 1);
     __syncthreads();
     if (!is_last) return;
     // one pass over the splits, up to 8 at a time; all loads of a group, for
@@ -741,19 +595,19 @@ __global__ __launch_bounds__(64 * NW, (decode_min_blocks<HG, KF, NW>())) void de
         Lsum[u] = 0.f;
         bad[u] = false;
     }
-    for (int s0 = 0; s0 < n_split; s0 += 8) {
-        const int cnt = n_split - s0 < 8 ? n_split - s0 : 8;
+    for (int s0 = 0; s0 < p.n_split; s0 += 8) {
+        const int cnt = p.n_split - s0 < 8 ? p.n_split - s0 : 8;
         float ms[kOut][8], ls[kOut][8], os[kOut][8];
 #pragma unroll
         for (int u = 0; u < kOut; ++u) {
             const int idx = threadIdx.x + u * kDecodeThreads;
             if (idx >= HG * DV) continue;
             const int h = idx / DV, c = idx % DV;
-            const float* base = p.ws + (part0 * HG + h) * ws_row;
+            const float* base = p.ws + ((size_t)b * p.Hq + h0 + h) * p.n_split * ws_row;
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 if (i < cnt) {
-                    const float* part = base + (size_t)(s0 + i) * HG * ws_row;
+                    const float* part = base + (size_t)(s0 + i) * ws_row;
                     ms[u][i] = load_coherent(part + DV);
                     ls[u][i] = load_coherent(part + DV + 1);
                     os[u][i] = load_coherent(part + c);
@@ -821,16 +675,6 @@ DecodePlan plan_decode(int B, int Hq, int Hkv, int max_ctx, int DV) {
     pl.counter_bytes = kCounterRegionBytes;
     pl.ws_bytes = pl.counter_bytes + (size_t)B * Hq * pl.n_split * (DV + 2) * sizeof(float);
     return pl;
-}
-
-// Two or three sequences of d_v 64 keep equal counts: their streams run at the same
-// rate either way, and what dealing costs itself shows (12 heads, r 16, 4-bit keys:
-// 128950 and 63716 tokens 65.5 us against 67.9 dealt; three up to 90000 from 4 % worse
-// to 8 % better; with four or more it wins, and with d_v 128 from two on: 60000 and
-// 29647 tokens, 32 heads over 8, 48.4 against 41.9).
-bool deal_splits(int B, int max_ctx, int DV, const DecodePlan& pl) {
-    return pl.n_split > 1 && B > (DV == 64 ? 3 : 1) && B <= kDealSequences && pl.split_len > kMinSplitTokens &&
-           (long)B * max_ctx <= 1L << 28;
 }
 
 // ------------------------------------------------------------------ fixed scratch

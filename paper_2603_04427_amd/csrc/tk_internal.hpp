@@ -26,13 +26,12 @@ struct DecodeParams {
     const uint16_t* v;          // value rows, DV bf16
     const int32_t* ctx_lens;    // [B]
     const int32_t* block_table; // [B, mb] or null
-    float* ws;                  // partials [Hq / HG, B * n_split, HG, DV + 2]
+    float* ws;                  // partials [B, Hq, n_split, DV + 2]
     unsigned* counters;         // [B, Hq] arrival counters (first B * Hq / HG used), zero between calls
     uint16_t* o;                // [B, Hq, DV] bf16
     int B, Hq, Hkv, G, max_ctx;
     int bs_log2, mb, num_blocks;
     int n_split;                // splits of each (sequence, head group): split s takes rounds s, s + n_split, ...
-    int deal;                   // nonzero: the splits are dealt to the sequences by length (deal_splits)
     float qscale;               // softmax scale * log2(e)
 };
 
@@ -46,10 +45,6 @@ struct DecodePlan {
 
 // Pure function of the shapes (no device query).
 DecodePlan plan_decode(int B, int Hq, int Hkv, int max_ctx, int DV);
-// Whether a plan's splits are dealt to the sequences by length: several sequences
-// (at most one a lane) with splits longer than the shortest ever dealt, and round
-// counts whose sums div_small divides exactly.
-bool deal_splits(int B, int max_ctx, int DV, const DecodePlan& pl);
 
 tk_status launch_decode(const DecodeParams& p, int R, int DV, int HG, int key_format, bool paged,
                         hipStream_t stream);

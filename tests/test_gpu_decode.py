@@ -215,21 +215,54 @@ def test_bad_block_table_entry_gives_nan_for_that_sequence():
 
 @pytest.mark.parametrize("paged,kdt", [(False, "bf16"), (True, "fp8")])
 @pytest.mark.parametrize("B,h_kv,ctx,lens", [
-    (16, 8, 2049, [2049, 257] + [0, 1, 128, 129, 700, 2048] * 2 + [1, 1]),  # two splits a sequence, one owed most
+    (16, 8, 2049, [2049, 257] + [0, 1, 128, 129, 700, 2048] * 2 + [1, 1]),  # two splits a sequence
     (8, 8, 4096, [4096, 3000, 17, 4096, 1, 512, 513, 2047]),                # four
-    (2, 2, 40000, [40000, 1]),                                              # 64: all but one go to the first
+    (2, 2, 40000, [40000, 1]),                                              # 40
     (5, 3, 20000, [1, 1, 1, 1, 20000]),
-    (64, 2, 3000, [3000] * 3 + list(range(0, 61 * 40, 40))),                # a sequence in every lane
-    (65, 2, 1500, [1500] + list(range(1, 65))),                             # more sequences than lanes: not dealt
-    (4, 8, 8192, [5000, 5000, 5000, 5001]),                                 # nearly equal
+    (64, 2, 3000, [3000] * 3 + list(range(0, 61 * 40, 40))),
+    (65, 2, 1500, [1500] + list(range(1, 65))),
+    (4, 8, 8192, [5000, 5000, 5000, 5001]),
 ])
-def test_splits_dealt_by_length(B, h_kv, ctx, lens, paged, kdt):
-    """Split contexts of sequences of unequal lengths, whose splits are dealt by length:
-    every output against the oracle, and the same bits from a second call."""
+def test_split_contexts_of_unequal_lengths(B, h_kv, ctx, lens, paged, kdt):
+    """Split contexts of sequences of unequal lengths, empty ones and ones shorter than
+    a split among them: every output against the oracle, and the same bits from a
+    second call."""
     dev = device()
     spec = with_shape(BASE, config_id=600 + B, batch=B, h_q=4 * h_kv, h_kv=h_kv, ctx=ctx, ctx_lens=tuple(lens),
                       k_dtype=kdt, paged=paged, block_size=64)
     out, ref = run_case(spec, structured=True)
-    gate(out, ref, kdt, f"dealt {spec}")
+    gate(out, ref, kdt, f"unequal {spec}")
     d = make_decode(spec, structured=True)
     assert torch.equal(decode_on_gpu(d, spec, dev), out)
+
+
+@pytest.mark.parametrize("paged,kdt,r,dv,G", [
+    (False, "bf16", 32, 128, 4), (True, "fp8", 32, 128, 4), (False, "int4", 32, 128, 4), (True, "int4", 64, 128, 4),
+    (False, "bf16", 16, 64, 1), (True, "fp8", 64, 64, 2), (False, "bf16", 128, 128, 2), (False, "fp8", 16, 128, 8),
+])
+def test_a_sequence_does_not_depend_on_its_neighbours(paged, kdt, r, dv, G):
+    """The split of the context depends only on the shapes: with the same slot, buffers and
+    max_ctx a sequence's output has the same bits whatever the other sequences' lengths
+    are, and a bad block-table entry of one changes no other."""
+    dev = device()
+    ctx, B, h_kv = 9000, 8, 4  # 6 splits of 1536 tokens
+    first = (9000, 5000, 700, 9000, 0, 3333, 1, 8999)
+    spec = with_shape(BASE, config_id=640 + r + G, batch=B, h_q=G * h_kv, h_kv=h_kv, ctx=ctx, ctx_lens=first, r=r, d_v=dv,
+                      k_dtype=kdt, paged=paged, block_size=64)
+    d = make_decode(spec, structured=True)
+    say(f"decode neighbours {spec}")
+    out = decode_on_gpu(d, spec, dev)
+    gate(out, decode_oracle(d, spec, None), kdt, f"neighbours {spec}")
+    for rest in ((9000,) * 6, (0,) * 6, (700, 1, 9000, 64, 65, 5000)):
+        lens = first[:2] + rest
+        d2 = dict(d)
+        d2["ctx_lens"] = torch.tensor(lens, dtype=torch.int32)
+        assert torch.equal(decode_on_gpu(d2, spec, dev)[:2], out[:2]), lens
+    if paged:
+        d2 = dict(d)
+        d2["block_table"] = d["block_table"].clone()
+        d2["block_table"][3, 70] = d["block_table"].numel() + 5
+        bad = decode_on_gpu(d2, spec, dev)
+        assert torch.isnan(bad[3].float()).all()
+        keep = [b for b in range(B) if b != 3]
+        assert torch.equal(bad[keep], out[keep])
