@@ -25,9 +25,9 @@ namespace tk {
 
 namespace {
 
+constexpr int kXcdCount = kXcds;
 constexpr int kPBK = 32;   // d_model per k-tile: 4 chunks of 8 bf16 per row
 constexpr int kStages = 3; // k-tiles in LDS: the one multiplied and two in flight
-constexpr int kXcdCount = 8;
 
 // A workgroup tile of BN output columns (weight rows) x BM tokens. Its waves are
 // laid out (BN / 64) x 2: each owns 64 columns x BM / 2 tokens.
@@ -475,61 +475,6 @@ __global__ __launch_bounds__(64 * NW, 1) void project_split_kernel(const Project
 
 }  // namespace
 
-// Tile shape of a call: the smallest of a ladder of tiles with which every CU gets
-// at most one workgroup. A workgroup's time grows with its columns plus tokens (both
-// are read over all of d_model), so small tiles win as long as CUs are free to take
-// more of them, and a second workgroup on some CUs costs more than the next larger
-// tile on all. Up to 32 x 64 the waves split d_model each for itself
-// (project_split_kernel), from 64 x 64 to 128 x 128 in groups that share a tile's
-// rows (project_kernel with KG > 1); the larger ones take d_model whole.
-// Measured, us per call (weights from HBM), with the shapes of one group only
-// (16 x 16 ... 64 x 64 by single waves, 128 x 128 up to 256 workgroups of the next) /
-// with this ladder:
-//   d_model 4096: 200 x 2048 columns 18.5 / 16.5, 600 x 1024 21.5 / 16.4, 1043 x 1024
-//     35.1 / 23.5, 600 x 2048 42.2 / 23.8, 4500 x 256 33.7 / 22.7, 2202 x 1024
-//     41.5 / 34.6, 9810 x 1024 118 / 97, 3000 x 4096 138 / 105
-//   d_model 768: 1043 x 768 6.5 / 5.8, 2202 x 768 9.8 / 7.5, 6500 x 768 16.9 / 15.2
-// Where a line lies: 32 x 64 against 64 x 64 at 192 and 256 tiles of the former,
-// d_model 4096: 17.2 / 16.0 and 18.5 / 16.5, at 160 16.4 / 15.5, at 136 equal. 64 x 128
-// against 128 x 64 (half the groups, twice the waves to a group): d_model 4096, 1500 x
-// 1024 23.3 / 27.4; 3072, 1500 x 768 19.7 / 21.9; 2048, 1500 x 1024 14.8 / 15.9; 1536,
-// 2202 x 768 11.7 / 10.8; 768, 2202 x 768 8.6 / 7.4. Just past 256 tiles of 256 x 256
-// their last ones run alone, and 256 x 128 are faster: 22000 x 768 from d_model 768
-// 54.3 / 47.2, 9810 x 2048 from 2048 110 / 102, 4500 x 4096 from 4096 200 / 193 (288
-// tiles); at 416 tiles 206 / 258.
-enum class ProjShape { k16x16, k16x32, k32x32, k32x64, k64x64, k64x128, k128x64, k128x128, k256x128, k256x256 };
-
-static long tiles_of(long M, long N, long BN, long BM) { return ((M + BM - 1) / BM) * ((N + BN - 1) / BN); }
-
-static ProjShape shape_of(long M, long N, long K) {
-    if (tiles_of(M, N, 16, 16) <= 256) return ProjShape::k16x16;
-    if (tiles_of(M, N, 16, 32) <= 256) return ProjShape::k16x32;
-    if (tiles_of(M, N, 32, 32) <= 256) return ProjShape::k32x32;
-    if (tiles_of(M, N, 32, 64) <= 160) return ProjShape::k32x64;
-    if (tiles_of(M, N, 64, 64) <= 256) return ProjShape::k64x64;
-    if (K < 2048 && tiles_of(M, N, 128, 64) <= 256) return ProjShape::k128x64;
-    if (tiles_of(M, N, 64, 128) <= 256) return ProjShape::k64x128;
-    if (tiles_of(M, N, 128, 128) <= 256) return ProjShape::k128x128;
-    if (tiles_of(M, N, 256, 128) <= 256) return ProjShape::k256x128;
-    const long large = tiles_of(M, N, 256, 256);
-    return large > 256 && large <= 320 ? ProjShape::k256x128 : ProjShape::k256x256;
-}
-
-long project_tiles(long M, long N, long K) {
-    switch (shape_of(M, N, K)) {
-        case ProjShape::k16x16: return tiles_of(M, N, 16, 16);
-        case ProjShape::k16x32: return tiles_of(M, N, 16, 32);
-        case ProjShape::k32x32: return tiles_of(M, N, 32, 32);
-        case ProjShape::k32x64: return tiles_of(M, N, 32, 64);
-        case ProjShape::k64x64: return tiles_of(M, N, 64, 64);
-        case ProjShape::k64x128: return tiles_of(M, N, 64, 128);
-        case ProjShape::k128x64: return tiles_of(M, N, 128, 64);
-        case ProjShape::k128x128: return tiles_of(M, N, 128, 128);
-        case ProjShape::k256x128: return tiles_of(M, N, 256, 128);
-        default: return tiles_of(M, N, 256, 256);
-    }
-}
-
 template <int BN, int BM, int NW, int D>
 static void run_split(const ProjectParams& p, dim3 grid, hipStream_t st) {
     hipLaunchKernelGGL((project_split_kernel<BN, BM, NW, D>), grid, dim3(64 * NW), 0, st, p);
@@ -542,7 +487,7 @@ static void run_tiles(const ProjectParams& p, dim3 grid, hipStream_t st) {
 tk_status launch_project(const ProjectParams& p, hipStream_t st) {
     // whole tiles per XCD: tail workgroups of the last XCDs exit at once
     const dim3 grid((unsigned)((p.tiles + kXcdCount - 1) / kXcdCount * kXcdCount));
-    switch (shape_of(p.M, p.N, p.K)) {
+    switch (project_shape(p.M, p.N, p.K)) {
         case ProjShape::k16x16: run_split<16, 16, 8, 4>(p, grid, st); break;
         case ProjShape::k16x32: run_split<16, 32, 8, 4>(p, grid, st); break;
         case ProjShape::k32x32: run_split<32, 32, 8, 4>(p, grid, st); break;
@@ -551,8 +496,9 @@ tk_status launch_project(const ProjectParams& p, hipStream_t st) {
         case ProjShape::k64x128: run_tiles<64, 128, 4>(p, grid, st); break;
         case ProjShape::k128x64: run_tiles<128, 64, 2>(p, grid, st); break;
         case ProjShape::k128x128: run_tiles<128, 128, 2>(p, grid, st); break;
+        case ProjShape::k128x128whole: run_tiles<128, 128, 1>(p, grid, st); break;
         case ProjShape::k256x128: run_tiles<256, 128, 1>(p, grid, st); break;
-        default: run_tiles<256, 256, 1>(p, grid, st);
+        case ProjShape::k256x256: run_tiles<256, 256, 1>(p, grid, st); break;
     }
     return hipGetLastError() == hipSuccess ? TK_OK : TK_ERR_HIP;
 }

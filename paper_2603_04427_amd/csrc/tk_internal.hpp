@@ -124,7 +124,6 @@ struct ProjectParams {
     int tiles;       // output tiles of the shape the call takes (project_tiles)
 };
 
-long project_tiles(long M, long N, long K);
 tk_status launch_project(const ProjectParams& p, hipStream_t stream);
 
 tk_status launch_prefill_bf16(const PrefillParams& p, int R, int DV, hipStream_t stream);

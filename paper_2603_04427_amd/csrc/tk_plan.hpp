@@ -257,4 +257,79 @@ constexpr DkdvForm dkdv_form(const AttnSizes& s) {
     return {4, 1, 64};
 }
 
+// ------------------------------------------------------------------ projection: tile ladder
+//
+// Tile shape of a call of M tokens x N columns over K = d_model: the smallest of a ladder
+// of tiles (columns x tokens) with which every CU gets at most one workgroup. A
+// workgroup's time grows with its columns plus tokens (both are read over all of
+// d_model), so small tiles win as long as CUs are free to take more of them, and a
+// second workgroup on some CUs costs more than the next larger tile on all. Up to 32 x 64
+// the waves split d_model each for itself (project_split_kernel), from 64 x 64 to 128 x
+// 128 in groups that share a tile's rows (project_kernel with KG > 1); the larger ones
+// take d_model whole. Measured, us per call (weights from HBM), with the shapes of one
+// group only (16 x 16 ... 64 x 64 by single waves, 128 x 128 up to 256 workgroups of the
+// next) / with this ladder:
+//   d_model 4096: 200 x 2048 columns 18.5 / 16.5, 600 x 1024 21.5 / 16.4, 1043 x 1024
+//     35.1 / 23.5, 600 x 2048 42.2 / 23.8, 4500 x 256 33.7 / 22.7, 2202 x 1024
+//     41.5 / 34.6, 9810 x 1024 118 / 97, 3000 x 4096 138 / 105
+//   d_model 768: 1043 x 768 6.5 / 5.8, 2202 x 768 9.8 / 7.5, 6500 x 768 16.9 / 15.2
+// Where a line lies:
+//   * 32 x 64 / 64 x 64 at 192 and 256 tiles of the former, d_model 4096: 17.2 / 16.0 and
+//     18.5 / 16.5, at 160 16.4 / 15.5, at 136 equal
+//   * 64 x 128 / 128 x 64 (half the groups, twice the waves to a group): d_model 4096,
+//     1500 x 1024 23.3 / 27.4; 3072, 1500 x 768 19.7 / 21.9; 2048, 1500 x 1024 14.8 / 15.9;
+//     1536, 2202 x 768 11.7 / 10.8; 768, 2202 x 768 8.6 / 7.4
+//   * past 256 tiles of 128 x 128: these without groups, two workgroups a CU, while 256 x
+//     128 would leave CUs idle and the weights are over 8 MiB, so that their stream from
+//     HBM needs the second workgroup to hide behind: d_model 4096, 1400 x 3072 (25 MB) 67.6
+//     / 80.8 with 256 x 128, 3004 x 2048 (17 MB) 70.5 / 80.9; 2048, 1816 x 3072 (13 MB) 40.0
+//     / 42.7; 4096, 6276 x 1024 (8.4 MB) 70.5 / 64.2, 12534 x 512 72.5 / 62.8
+//   * just past 256 tiles of 256 x 256 their last ones run alone, and 256 x 128 are
+//     faster: 22000 x 768 from d_model 768 54.3 / 47.2, 9810 x 2048 from 2048 110 / 102,
+//     4500 x 4096 from 4096 200 / 193 (288 tiles); at 416 tiles 206 / 258
+enum class ProjShape : int {
+    k16x16, k16x32, k32x32, k32x64, k64x64, k64x128, k128x64, k128x128, k128x128whole, k256x128, k256x256
+};
+
+struct ProjTileSize {
+    int columns, tokens;
+};
+constexpr ProjTileSize project_tile(ProjShape s) {
+    switch (s) {
+        case ProjShape::k16x16: return {16, 16};
+        case ProjShape::k16x32: return {16, 32};
+        case ProjShape::k32x32: return {32, 32};
+        case ProjShape::k32x64: return {32, 64};
+        case ProjShape::k64x64: return {64, 64};
+        case ProjShape::k64x128: return {64, 128};
+        case ProjShape::k128x64: return {128, 64};
+        case ProjShape::k128x128:
+        case ProjShape::k128x128whole: return {128, 128};
+        case ProjShape::k256x128: return {256, 128};
+        case ProjShape::k256x256: break;
+    }
+    return {256, 256};
+}
+constexpr long project_tiles_of(long M, long N, ProjShape s) {
+    const ProjTileSize t = project_tile(s);
+    return ((M + t.tokens - 1) / t.tokens) * ((N + t.columns - 1) / t.columns);
+}
+
+constexpr ProjShape project_shape(long M, long N, long K) {
+    const auto tiles = [=](ProjShape s) { return project_tiles_of(M, N, s); };
+    if (tiles(ProjShape::k16x16) <= 256) return ProjShape::k16x16;
+    if (tiles(ProjShape::k16x32) <= 256) return ProjShape::k16x32;
+    if (tiles(ProjShape::k32x32) <= 256) return ProjShape::k32x32;
+    if (tiles(ProjShape::k32x64) <= 160) return ProjShape::k32x64;
+    if (tiles(ProjShape::k64x64) <= 256) return ProjShape::k64x64;
+    if (K < 2048 && tiles(ProjShape::k128x64) <= 256) return ProjShape::k128x64;
+    if (tiles(ProjShape::k64x128) <= 256) return ProjShape::k64x128;
+    if (tiles(ProjShape::k128x128) <= 256) return ProjShape::k128x128;
+    if (tiles(ProjShape::k256x128) < 256 && N * K * 2 > (8L << 20)) return ProjShape::k128x128whole;
+    if (tiles(ProjShape::k256x128) <= 256) return ProjShape::k256x128;
+    const long large = tiles(ProjShape::k256x256);
+    return large > 256 && large <= 320 ? ProjShape::k256x128 : ProjShape::k256x256;
+}
+constexpr long project_tiles(long M, long N, long K) { return project_tiles_of(M, N, project_shape(M, N, K)); }
+
 }  // namespace tk

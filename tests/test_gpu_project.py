@@ -7,8 +7,9 @@ oracle on the same seeded inputs (Sec. 2.3, Eq. 6-7).
   exact products (at most d_model * 2^-24 of sum |x||w|) and one rounding to
   bf16 (at most 2^-8 of the value):
       |Y_gpu - Y| <= 2^-8 |Y| + (1 + 2^-8) d_model 2^-24 (|X| |W|).
-  Shapes cover every tile shape the kernel picks, tile tails in tokens and
-  columns, odd numbers of k-tiles, head widths 4-128 and a single token.
+  Shapes cover every tile shape the kernel picks (test_plan.py holds them to the
+  rule), tile tails in tokens and columns, odd numbers of k-tiles, head widths 4-136
+  and a single token.
 * The converted layer: factor.factor_layer on a layer whose key heads have exact
   rank r, then factor.project_thin (three kernel calls) against
   oracle.factored.thin_projections, which redoes the SVD with numpy in fp64.
@@ -46,42 +47,48 @@ def check(got, ref, bar, what):
     return np.abs(g - ref).max()
 
 
-SHAPES = [  # (B, S, d_model, heads, width)
-    (1, 256, 768, 12, 16),    # GPT-2 small: q' and k' (r 16 per head)
-    (1, 256, 768, 12, 64),    # GPT-2 small: values
-    (2, 300, 1024, 8, 32),    # GQA-like queries, ragged token tile
-    (2, 300, 1024, 2, 128),   # full-width values of 2 KV heads
-    (3, 77, 4096, 32, 32),    # Mistral-7B d_model, 32 query heads of r 32
-    (1, 1, 64, 1, 4),         # one token, one narrow head
-    (1, 129, 160, 3, 20),     # an odd number of 32-wide k-tiles, 60 columns, ragged tokens
-    (2, 2048, 1024, 32, 128),  # 256 x 256 workgroup tiles (at least one per CU)
-    (1, 4100, 256, 64, 68),   # 256 x 256 tiles with tails in tokens and columns
-    (1, 4100, 160, 64, 68),   # 256 x 256 tiles over an odd number (5) of k-tiles
-    (1, 4096, 32, 64, 64),    # 256 x 256 tiles over a single k-tile
-    (2, 16350, 288, 7, 36),   # 256 x 128 tiles (narrow and long): ragged columns and tokens, 9 k-tiles
-    # tiles whose waves split d_model (few tokens), then 128 x 128 tiles
-    (1, 1, 32, 5, 4),         # 16 x 16: a single k-step, 20 columns
-    (16, 1, 4096, 32, 32),    # 16 x 16: a decode step, one token per sequence
-    (1, 17, 96, 3, 20),       # 16 x 16: 3 k-steps, tails
-    (1, 100, 544, 33, 20),    # 16 x 32: 17 k-steps, tails
-    (1, 150, 1056, 33, 28),   # 32 x 32: 33 k-steps, tails
-    (2, 170, 288, 33, 28),    # 32 x 64: 9 k-steps, tails
-    (1, 1000, 224, 33, 28),   # 64 x 64: 7 k-steps, tails
-    (1, 2500, 160, 15, 68),   # 128 x 128: 5 k-tiles, tails
+SHAPES = [  # (B, S, d_model, heads, width), the tile the kernel takes (columns x tokens)
+    ((1, 256, 768, 12, 16), "16x16"),             # GPT-2 small: q' and k' (r 16 per head)
+    ((1, 256, 768, 12, 64), "32x32"),             # GPT-2 small: values
+    ((2, 300, 1024, 8, 32), "32x32"),             # GQA-like queries, ragged token tile
+    ((2, 300, 1024, 2, 128), "32x32"),            # full-width values of 2 KV heads
+    ((3, 77, 4096, 32, 32), "32x32"),             # Mistral-7B d_model, 32 query heads of r 32
+    ((1, 1, 64, 1, 4), "16x16"),                  # one token, one narrow head
+    ((1, 129, 160, 3, 20), "16x16"),              # an odd number of 32-wide k-tiles, 60 columns, ragged tokens
+    ((2, 2048, 1024, 32, 128), "256x256"),        # one tile per CU
+    ((1, 4100, 256, 64, 68), "256x128"),          # tails in tokens and columns
+    ((1, 4100, 160, 64, 68), "256x128"),          # an odd number (5) of k-tiles
+    ((1, 4096, 32, 64, 64), "256x256"),           # a single k-tile
+    ((2, 16350, 288, 7, 36), "256x128"),          # narrow and long: ragged columns and tokens, 9 k-tiles
+    # few tokens: tiles whose waves split d_model
+    ((1, 1, 32, 5, 4), "16x16"),                  # a single k-step, 20 columns
+    ((16, 1, 4096, 32, 32), "16x16"),             # a decode step, one token per sequence
+    ((1, 17, 96, 3, 20), "16x16"),                # 3 k-steps, tails
+    ((1, 100, 544, 33, 20), "16x32"),             # 17 k-steps, tails
+    ((1, 150, 1056, 33, 28), "32x32"),            # 33 k-steps, tails
+    ((2, 150, 288, 33, 28), "32x64"),             # 9 k-steps, tails
+    ((1, 300, 160, 15, 68), "32x64"),             # 5 k-steps: fewer granules than waves, an odd last one
+    ((1, 310, 2080, 15, 68), "32x64"),            # 65 k-steps, tails
+    ((1, 1177, 4096, 3, 76), "32x64"),            # 16 k-steps a wave, narrow
+    ((1, 1000, 224, 33, 28), "64x64"),            # 7 k-steps, tails
+    ((1, 2500, 160, 15, 68), "128x128"),          # 5 k-tiles, tails
     # tiles whose k-tiles are shared out among groups of waves
-    (1, 1000, 32, 33, 28),    # 64 x 64: one k-tile for four groups
-    (1, 1000, 288, 33, 28),   # 64 x 64: 9 k-tiles, one group with one more
-    (1, 1500, 96, 33, 28),    # 128 x 64: 3 k-tiles for two groups
-    (3, 200, 2080, 101, 20),  # 64 x 128: 65 k-tiles for four groups
-    (1, 9000, 64, 12, 16),    # 64 x 128, narrow: 2 k-tiles, groups without any
-    (1, 2500, 32, 15, 68),    # 128 x 128: one k-tile for two groups
-    (2, 3000, 96, 15, 68),    # 256 x 128: 3 k-tiles
-    (1, 4700, 96, 64, 68),    # 256 x 256: more than 320 tiles
+    ((1, 1000, 32, 33, 28), "64x64"),             # one k-tile for four groups
+    ((1, 1000, 288, 33, 28), "64x64"),            # 9 k-tiles, one group with one more
+    ((1, 1500, 96, 33, 28), "128x64"),            # 3 k-tiles for two groups
+    ((3, 200, 2080, 101, 20), "64x128"),          # 65 k-tiles for four groups
+    ((1, 9000, 64, 12, 16), "64x128"),            # narrow: 2 k-tiles, groups without any
+    ((1, 2500, 32, 15, 68), "128x128"),           # one k-tile for two groups
+    ((1, 1300, 2080, 31, 132), "128x128 whole"),  # two workgroups a CU, 65 k-tiles, tails
+    ((1, 1400, 3072, 23, 136), "128x128 whole"),  # and 96 k-tiles
+    ((2, 3000, 96, 15, 68), "256x128"),           # 3 k-tiles
+    ((1, 4700, 96, 64, 68), "256x256"),           # more than 320 tiles
+    ((1, 5200, 160, 33, 132), "256x256"),         # and tails in tokens and columns, 5 k-tiles
 ]
 
 
-@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
-def test_projection_against_oracle(shape):
+@pytest.mark.parametrize("shape,tile", SHAPES, ids=lambda s: "x".join(map(str, s)) if isinstance(s, tuple) else s)
+def test_projection_against_oracle(shape, tile):
     B, S, d_model, heads, width = shape
     dev = device()
     seed = 1600 + sum(shape)
@@ -90,7 +97,7 @@ def test_projection_against_oracle(shape):
     xd, wd = x.double().numpy(), w.double().numpy()
     ref = factored.project_heads(xd, wd, heads)
     bar = U * np.abs(ref) + (1 + U) * d_model * 2.0 ** -24 * factored.project_heads(np.abs(xd), np.abs(wd), heads)
-    say(f"project {shape}")
+    say(f"project {shape} {tile}")
     y = tk_project_heads(x.to(dev), w.t().contiguous().to(dev), heads)
     torch.cuda.synchronize()
     assert tuple(y.shape) == (B, heads, S, width)

@@ -16,6 +16,14 @@ QUERIES = r"""
 #include "tk_plan.hpp"
 using namespace tk;
 extern "C" {
+void projection(long M, long N, long K, int* out) {
+    const ProjShape s = project_shape(M, N, K);
+    const ProjTileSize t = project_tile(s);
+    out[0] = t.columns;
+    out[1] = t.tokens;
+    out[2] = s == ProjShape::k128x128whole;
+    out[3] = (int)project_tiles(M, N, K);
+}
 void place(int order, int block, int pairs, int n, int* out) {
     const Place p = place_workgroup(order, block, pairs, n);
     out[0] = p.pair;
@@ -211,3 +219,36 @@ def test_dq_form_of_measured_calls(plan, call, form):
 ])
 def test_dkdv_form_of_measured_calls(plan, call, form):
     assert plan.dkdv_shape(*call) == form
+
+
+def test_projection_shapes_of_the_parity_test_cover_every_tile(plan):
+    """Each entry of the GPU parity test runs the tile it is listed with, and every tile
+    of the ladder has one."""
+    from test_gpu_project import SHAPES
+    out = (ctypes.c_int * 4)()
+    for (B, S, d_model, heads, width), tile in SHAPES:
+        plan.projection(ctypes.c_long(B * S), ctypes.c_long(heads * width), ctypes.c_long(d_model), out)
+        assert f"{out[0]}x{out[1]}" + (" whole" if out[2] else "") == tile, (B, S, d_model, heads, width)
+        assert out[3] == -(-B * S // out[1]) * -(-heads * width // out[0])
+    assert {tile for _, tile in SHAPES} == {"16x16", "16x32", "32x32", "32x64", "64x64", "64x128", "128x64", "128x128",
+                                            "128x128 whole", "256x128", "256x256"}
+
+
+@pytest.mark.parametrize("M,N,K,tile", [
+    (16, 1024, 4096, "16x16"),
+    (200, 2048, 4096, "64x64"),
+    (418, 768, 4096, "64x64"),        # 168 tiles of 32 x 64
+    (1500, 1024, 4096, "64x128"),
+    (2202, 768, 768, "128x64"),
+    (1400, 3072, 4096, "128x128 whole"),
+    (3004, 2048, 4096, "128x128 whole"),
+    (6276, 1024, 4096, "256x128"),    # 8 MiB of weights
+    (12534, 512, 4096, "256x128"),
+    (3000, 4096, 4096, "256x256"),
+    (4500, 4096, 4096, "256x128"),    # 288 tiles of 256 x 256
+    (32768, 1024, 4096, "256x256"),
+])
+def test_projection_tile_of_measured_calls(plan, M, N, K, tile):
+    out = (ctypes.c_int * 4)()
+    plan.projection(ctypes.c_long(M), ctypes.c_long(N), ctypes.c_long(K), out)
+    assert f"{out[0]}x{out[1]}" + (" whole" if out[2] else "") == tile
