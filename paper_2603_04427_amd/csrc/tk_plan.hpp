@@ -274,8 +274,11 @@ constexpr DkdvForm dkdv_form(const AttnSizes& s) {
 //     41.5 / 34.6, 9810 x 1024 118 / 97, 3000 x 4096 138 / 105
 //   d_model 768: 1043 x 768 6.5 / 5.8, 2202 x 768 9.8 / 7.5, 6500 x 768 16.9 / 15.2
 // Where a line lies:
-//   * 32 x 64 / 64 x 64 at 192 and 256 tiles of the former, d_model 4096: 17.2 / 16.0 and
-//     18.5 / 16.5, at 160 16.4 / 15.5, at 136 equal
+//   * 32 x 64 / 64 x 64: at d_model 4096 they cross between 120 and 200 tiles of the
+//     former, by tokens and columns (637 x 384, 120 tiles 15.2 / 15.0; 1177 x 228, 152
+//     14.5 / 14.7; 418 x 768, 168 16.6 / 15.8; 158 x 2048, 192 17.8 / 19.4; 1706 x 256,
+//     216 16.9 / 15.1), at 2048 by 256 (94 x 4096 13.3 / 12.4), at 8192 by 192 (332 x 1024
+//     30.3 / 30.4), and below 2048 past 256 (2035 x 256 5.9 / 6.2)
 //   * 64 x 128 / 128 x 64 (half the groups, twice the waves to a group): d_model 4096,
 //     1500 x 1024 23.3 / 27.4; 3072, 1500 x 768 19.7 / 21.9; 2048, 1500 x 1024 14.8 / 15.9;
 //     1536, 2202 x 768 11.7 / 10.8; 768, 2202 x 768 8.6 / 7.4
@@ -320,7 +323,7 @@ constexpr ProjShape project_shape(long M, long N, long K) {
     if (tiles(ProjShape::k16x16) <= 256) return ProjShape::k16x16;
     if (tiles(ProjShape::k16x32) <= 256) return ProjShape::k16x32;
     if (tiles(ProjShape::k32x32) <= 256) return ProjShape::k32x32;
-    if (tiles(ProjShape::k32x64) <= 160) return ProjShape::k32x64;
+    if (tiles(ProjShape::k32x64) <= (K < 2048 ? 256 : 160)) return ProjShape::k32x64;
     if (tiles(ProjShape::k64x64) <= 256) return ProjShape::k64x64;
     if (K < 2048 && tiles(ProjShape::k128x64) <= 256) return ProjShape::k128x64;
     if (tiles(ProjShape::k64x128) <= 256) return ProjShape::k64x128;

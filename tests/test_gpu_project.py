@@ -67,6 +67,7 @@ SHAPES = [  # (B, S, d_model, heads, width), the tile the kernel takes (columns 
     ((1, 100, 544, 33, 20), "16x32"),             # 17 k-steps, tails
     ((1, 150, 1056, 33, 28), "32x32"),            # 33 k-steps, tails
     ((2, 150, 288, 33, 28), "32x64"),             # 9 k-steps, tails
+    ((2, 240, 288, 33, 28), "32x64"),             # more than 160 tiles
     ((1, 300, 160, 15, 68), "32x64"),             # 5 k-steps: fewer granules than waves, an odd last one
     ((1, 310, 2080, 15, 68), "32x64"),            # 65 k-steps, tails
     ((1, 1177, 4096, 3, 76), "32x64"),            # 16 k-steps a wave, narrow
