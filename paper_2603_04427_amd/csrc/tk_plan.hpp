@@ -278,7 +278,8 @@ constexpr DkdvForm dkdv_form(const AttnSizes& s) {
 //     former, by tokens and columns (637 x 384, 120 tiles 15.2 / 15.0; 1177 x 228, 152
 //     14.5 / 14.7; 418 x 768, 168 16.6 / 15.8; 158 x 2048, 192 17.8 / 19.4; 1706 x 256,
 //     216 16.9 / 15.1), at 2048 by 256 (94 x 4096 13.3 / 12.4), at 8192 by 192 (332 x 1024
-//     30.3 / 30.4), and below 2048 past 256 (2035 x 256 5.9 / 6.2)
+//     30.3 / 30.4), at 1024 and 1536 between 192 and 256 (255 x 2048 from 1536, 256 tiles
+//     9.6 / 8.9; 196 x 2048 from 1024 7.4 / 7.2), and at 768 past 256 (2035 x 256 5.9 / 6.2)
 //   * 64 x 128 / 128 x 64 (half the groups, twice the waves to a group): d_model 4096,
 //     1500 x 1024 23.3 / 27.4; 3072, 1500 x 768 19.7 / 21.9; 2048, 1500 x 1024 14.8 / 15.9;
 //     1536, 2202 x 768 11.7 / 10.8; 768, 2202 x 768 8.6 / 7.4
@@ -323,7 +324,7 @@ constexpr ProjShape project_shape(long M, long N, long K) {
     if (tiles(ProjShape::k16x16) <= 256) return ProjShape::k16x16;
     if (tiles(ProjShape::k16x32) <= 256) return ProjShape::k16x32;
     if (tiles(ProjShape::k32x32) <= 256) return ProjShape::k32x32;
-    if (tiles(ProjShape::k32x64) <= (K < 2048 ? 256 : 160)) return ProjShape::k32x64;
+    if (tiles(ProjShape::k32x64) <= (K < 1024 ? 256 : K < 2048 ? 192 : 160)) return ProjShape::k32x64;
     if (tiles(ProjShape::k64x64) <= 256) return ProjShape::k64x64;
     if (K < 2048 && tiles(ProjShape::k128x64) <= 256) return ProjShape::k128x64;
     if (tiles(ProjShape::k64x128) <= 256) return ProjShape::k64x128;

@@ -239,6 +239,7 @@ def test_projection_shapes_of_the_parity_test_cover_every_tile(plan):
     (200, 2048, 4096, "64x64"),
     (418, 768, 4096, "64x64"),        # 168 tiles of 32 x 64
     (2035, 256, 768, "32x64"),        # 256 of them
+    (255, 2048, 1536, "64x64"),
     (1500, 1024, 4096, "64x128"),
     (2202, 768, 768, "128x64"),
     (1400, 3072, 4096, "128x128 whole"),
