@@ -8,8 +8,9 @@ library has not been built, the first call raises instead of falling back.
 
 The plain calls first go to _tkcall (csrc/torch_call.cpp), which does the same
 marshalling in C++ for plain tensors on the current stream and declines the rest;
-what it declines is marshalled here, through ctypes, and raises here if it is
-wrong. A prepared call is bound there once and then launches without conversions.
+what it declines is checked and marshalled here, as a prepared call, and raises here
+if it is wrong. Prepared calls are launched by _tkcall too, with the arguments read
+from their tuple each time.
 Small calls were bound by this module's host work: a projection of 3 tokens took
 11 us a call, an append of 2 rows 13, a 32-token prefill 12.4 (kernels of 2 to 5).
 """
@@ -51,6 +52,7 @@ SIGNATURES = {
 _CONNECTED = ("tk_attn_prefill", "tk_attn_prefill_lse", "tk_attn_prefill_backward",
               "tk_attn_prefill_backward_workspace_bytes", "tk_attn_decode", "tk_attn_decode_noalloc",
               "tk_cache_append", "tk_project_heads")
+_BOUND = frozenset(n for n in _CONNECTED if SIGNATURES[n][1] is _i)  # those that return a status
 _CALL_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "_tkcall.so")
 
 _lib = None
@@ -137,7 +139,11 @@ def _check(t: torch.Tensor, name: str, dtypes, ndim: int):
 
 class PreparedCall:
     """A C entry point with its arguments marshalled once; calling it launches again
-    with the same tensors (for timing loops and graph-free replay)."""
+    with the same tensors (for timing loops and graph-free replay).
+
+    It is ``fn(*args)``: both can be replaced, and so can the values that the arguments
+    hold. _tkcall makes that call where it can, which is where ``fn`` is the library's own
+    and ``args`` a tuple of what the ``prepare_`` functions put there."""
 
     def __init__(self, name: str, args, keep, result=None):
         self.name = name
@@ -145,13 +151,22 @@ class PreparedCall:
         self.args = args
         self.keep = keep  # tensors whose memory the pointers refer to
         self.result = keep[-1] if result is None else result
-        self._bound = self._bound_args = None
+        self._bound = self._bound_to = None
+
+    def _bind(self):
+        self._bound, self._bound_to = None, (self.fn, self.args)
+        if (self.name in _BOUND and self.fn is getattr(lib(), self.name) and type(self.args) is tuple
+                and all(type(a) in (int, float, type(None), _vp) for a in self.args)):
+            try:
+                self._bound = (_call or _load_call()).bind(self.name, self.args)
+            except TypeError:  # ctypes says what is wrong with them
+                pass
 
     def __call__(self):
-        if self._bound_args is not self.args:
-            self._bound = (_call or _load_call()).bind(self.name, self.args)
-            self._bound_args = self.args
-        st = self._bound()
+        to = self._bound_to
+        if to is None or to[0] is not self.fn or to[1] is not self.args:
+            self._bind()
+        st = self._bound() if self._bound is not None else self.fn(*self.args)
         if st != TK_OK:
             raise TkError(st, self.name)
         return self.result

@@ -12,7 +12,8 @@
 //       dispatch modes): binding.py then marshals it, and raises what is wrong with
 //       it. A C status other than TK_OK is returned as an int.
 //   bind(name, args)
-//       a callable that repeats one marshalled C call and returns its status.
+//       a callable that makes the C call with the tuple's arguments and returns its
+//       status. It reads them anew each time (a ctypes object's value can be set).
 //
 // The library's functions are reached through addresses set by connect(), which
 // binding.py takes from the library it has loaded: one copy of it per process.
@@ -289,24 +290,14 @@ PyObject* cache_append(PyObject*, PyObject* const* a, Py_ssize_t n) {
 
 // ------------------------------------------------------------------ bound calls
 
-struct Call {
-    virtual ~Call() = default;
-    virtual tk_status run() const = 0;
-};
-template <class... A>
-struct Bound : Call {
-    tk_status (*fn)(A...);
-    std::tuple<A...> args;
-    tk_status run() const override { return std::apply(fn, args); }
-};
-
 // One marshalled argument (an int, a float, None, or a ctypes object holding one),
 // converted as ctypes does: integers modulo the type's width.
 template <class T>
 bool convert(PyObject* o, T& out) {
+    static PyObject* const value = PyUnicode_InternFromString("value");
     THPObjectPtr held;
     if (o != Py_None && !PyLong_Check(o) && !PyFloat_Check(o)) {
-        held = PyObject_GetAttrString(o, "value");
+        held = PyObject_GetAttr(o, value);
         if (!held) return false;
         o = held.get();
     }
@@ -316,7 +307,7 @@ bool convert(PyObject* o, T& out) {
         out = (float)v;
     } else {
         const unsigned long long v = o == Py_None ? 0 : PyLong_AsUnsignedLongLongMask(o);
-        if (PyErr_Occurred()) return false;
+        if (v == (unsigned long long)-1 && PyErr_Occurred()) return false;
         if constexpr (std::is_pointer_v<T>)
             out = (T)(uintptr_t)v;
         else
@@ -324,37 +315,50 @@ bool convert(PyObject* o, T& out) {
     }
     return true;
 }
-template <class... A, size_t... I>
-Call* bind_to(tk_status (*fn)(A...), PyObject* args, std::index_sequence<I...>) {
-    if (PyTuple_GET_SIZE(args) != (Py_ssize_t)sizeof...(A)) {
-        PyErr_SetString(PyExc_TypeError, "wrong number of arguments");
-        return nullptr;
-    }
-    auto call = std::make_unique<Bound<A...>>();
-    call->fn = fn;
-    if (!(convert(PyTuple_GET_ITEM(args, I), std::get<I>(call->args)) && ...)) return nullptr;
-    return call.release();
-}
+
+// An entry point called with a tuple's arguments: its status, or -1 with an error set
+// (`launch` false: they are only converted).
+struct Call {
+    virtual ~Call() = default;
+    virtual int run(PyObject* args, bool launch) const = 0;
+};
 template <class... A>
-Call* bind_call(tk_status (*fn)(A...), PyObject* args) {
-    return bind_to(fn, args, std::index_sequence_for<A...>{});
+struct Bound : Call {
+    tk_status (*fn)(A...);
+    explicit Bound(tk_status (*f)(A...)) : fn(f) {}
+    int run(PyObject* args, bool launch) const override { return run(args, launch, std::index_sequence_for<A...>{}); }
+    template <size_t... I>
+    int run(PyObject* args, bool launch, std::index_sequence<I...>) const {
+        if (PyTuple_GET_SIZE(args) != (Py_ssize_t)sizeof...(A)) {
+            PyErr_SetString(PyExc_TypeError, "wrong number of arguments");
+            return -1;
+        }
+        std::tuple<A...> v;
+        if (!(convert(PyTuple_GET_ITEM(args, I), std::get<I>(v)) && ...)) return -1;
+        if (!launch) return TK_OK;
+        NoGil nogil;
+        return std::apply(fn, v);
+    }
+};
+template <class... A>
+std::unique_ptr<Call> call_of(tk_status (*fn)(A...)) {
+    return std::make_unique<Bound<A...>>(fn);
 }
 
 struct BoundObject {
     PyObject_HEAD
     Call* call;
+    PyObject* args;
 };
 void bound_dealloc(PyObject* self) {
     delete ((BoundObject*)self)->call;
+    Py_XDECREF(((BoundObject*)self)->args);
     Py_TYPE(self)->tp_free(self);
 }
 PyObject* bound_call(PyObject* self, PyObject*, PyObject*) {
-    tk_status st;
-    {
-        NoGil nogil;
-        st = ((BoundObject*)self)->call->run();
-    }
-    return status_of(st);
+    const BoundObject* b = (const BoundObject*)self;
+    const int st = b->call->run(b->args, true);
+    return st < 0 ? nullptr : PyLong_FromLong(st);
 }
 PyTypeObject BoundType = {PyVarObject_HEAD_INIT(nullptr, 0)};
 
@@ -365,30 +369,28 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
         return nullptr;
     }
     const std::string name = PyUnicode_AsUTF8(a[0]);
-    Call* call = nullptr;
+    std::unique_ptr<Call> call;
     if (name == "tk_attn_prefill")
-        call = bind_call(g.prefill, a[1]);
+        call = call_of(g.prefill);
     else if (name == "tk_attn_prefill_lse")
-        call = bind_call(g.prefill_lse, a[1]);
+        call = call_of(g.prefill_lse);
     else if (name == "tk_attn_prefill_backward")
-        call = bind_call(g.prefill_backward, a[1]);
+        call = call_of(g.prefill_backward);
     else if (name == "tk_attn_decode")
-        call = bind_call(g.decode, a[1]);
+        call = call_of(g.decode);
     else if (name == "tk_attn_decode_noalloc")
-        call = bind_call(g.decode_noalloc, a[1]);
+        call = call_of(g.decode_noalloc);
     else if (name == "tk_cache_append")
-        call = bind_call(g.append, a[1]);
+        call = call_of(g.append);
     else if (name == "tk_project_heads")
-        call = bind_call(g.project, a[1]);
+        call = call_of(g.project);
     else
-        PyErr_Format(PyExc_ValueError, "no entry point %s", name.c_str());
-    if (!call) return nullptr;
+        return PyErr_Format(PyExc_ValueError, "no entry point %s", name.c_str());
+    if (call->run(a[1], false) < 0) return nullptr;
     BoundObject* o = PyObject_New(BoundObject, &BoundType);
-    if (!o) {
-        delete call;
-        return nullptr;
-    }
-    o->call = call;
+    if (!o) return nullptr;
+    o->call = call.release();
+    o->args = Py_NewRef(a[1]);
     return (PyObject*)o;
     END_HANDLE_TH_ERRORS
 }

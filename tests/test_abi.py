@@ -287,3 +287,38 @@ def test_backward_refuses_before_it_launches_anything():
     threads that one launch takes, and 9.4 M row blocks, which would fit."""
     big = dict(batch=1 << 20, H_q=9, H_kv=9, seq_q=1, seq_k=129, ws_bytes=1 << 40)
     assert backward(**big) == tb.TK_ERR_UNSUPPORTED
+
+
+def test_prepared_calls_are_their_fn_and_args():
+    """A prepared call is fn(*args) at the time of the call, whatever has been replaced since."""
+    pointer = ctypes.c_void_p(P.value)
+    good = (P, pointer, P, 0, 8, 64, 2, 32, None)   # no rows: nothing to launch
+    for args in (good, list(good)):
+        pointer.value = P.value
+        call = tb.PreparedCall("tk_project_heads", args, ("kept",))
+        assert call() == "kept" and call() == "kept"
+        call.args = args[:3] + type(args)((2,)) + args[4:]
+        pointer.value = P_ODD.value                  # an argument's value, set in place
+        with pytest.raises(tb.TkError) as e:
+            call()
+        assert e.value.status == tb.TK_ERR_INVALID_ARG
+        seen = []
+        call.fn = lambda *a: seen.append(a) or tb.TK_OK
+        assert call() == "kept" and tuple(seen[0]) == tuple(call.args)
+        call.fn = getattr(tb.lib(), "tk_project_heads")
+        call.args = args
+        pointer.value = None                         # no rows: not looked at
+        assert call() == "kept"
+    listed = list(good)
+    call = tb.PreparedCall("tk_project_heads", listed, ("kept",))
+    assert call() == "kept"
+    listed[3] = -1
+    with pytest.raises(tb.TkError):
+        call()
+    with pytest.raises(tb.TkError, match="status 100"):  # any exported function
+        tb.PreparedCall("tk_version", (), ("kept",))()
+    for wrong in (good[:-1], good[:3] + (1.5,) + good[4:], good[:3] + ("2",) + good[4:]):
+        with pytest.raises((TypeError, ctypes.ArgumentError)):
+            tb.PreparedCall("tk_project_heads", wrong, ("kept",))()
+    with pytest.raises(AttributeError):
+        tb.PreparedCall("tk_no_such_entry", (), ("kept",))
