@@ -147,7 +147,7 @@ class PreparedCall:
 
     def __init__(self, name: str, args, keep, result=None):
         self.name = name
-        self.fn = getattr(lib(), name)
+        self.fn = self._entry = getattr(lib(), name)
         self.args = args
         self.keep = keep  # tensors whose memory the pointers refer to
         self.result = keep[-1] if result is None else result
@@ -155,10 +155,10 @@ class PreparedCall:
 
     def _bind(self):
         self._bound, self._bound_to = None, (self.fn, self.args)
-        if (self.name in _BOUND and self.fn is getattr(lib(), self.name) and type(self.args) is tuple
-                and all(type(a) in (int, float, type(None), _vp) for a in self.args)):
+        native = _call or _load_call()
+        if self.fn is self._entry and self.name in _BOUND and native.plain_args(self.args):
             try:
-                self._bound = (_call or _load_call()).bind(self.name, self.args)
+                self._bound = native.bind(self.name, self.args)
             except TypeError:  # ctypes says what is wrong with them
                 pass
 

@@ -14,6 +14,8 @@
 //   bind(name, args)
 //       a callable that makes the C call with the tuple's arguments and returns its
 //       status. It reads them anew each time (a ctypes object's value can be set).
+//   plain_args(args)
+//       whether they are a tuple of ints, floats, None and ctypes pointers alone.
 //
 // The library's functions are reached through addresses set by connect(), which
 // binding.py takes from the library it has loaded: one copy of it per process.
@@ -395,6 +397,22 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
     END_HANDLE_TH_ERRORS
 }
 
+// (args): whether bind() reads them as ctypes would, each being exactly one of the
+// types that it converts
+PyObject* plain_args(PyObject*, PyObject* args) {
+    static PyObject* const pointer = [] {
+        THPObjectPtr ctypes(PyImport_ImportModule("ctypes"));
+        return ctypes ? PyObject_GetAttrString(ctypes.get(), "c_void_p") : nullptr;
+    }();
+    if (!pointer) return nullptr;
+    bool plain = PyTuple_CheckExact(args);
+    for (Py_ssize_t i = 0; plain && i < PyTuple_GET_SIZE(args); ++i) {
+        PyObject* o = PyTuple_GET_ITEM(args, i);
+        plain = o == Py_None || PyLong_CheckExact(o) || PyFloat_CheckExact(o) || (PyObject*)Py_TYPE(o) == pointer;
+    }
+    return PyBool_FromLong(plain);
+}
+
 // connect(address of each entry point, in this order)
 PyObject* connect(PyObject*, PyObject* const* a, Py_ssize_t n) {
     void** const to[] = {(void**)&g.prefill, (void**)&g.prefill_lse, (void**)&g.prefill_backward,
@@ -417,7 +435,8 @@ PyObject* connect(PyObject*, PyObject* const* a, Py_ssize_t n) {
 
 #define METHOD(f) {#f, (PyCFunction)(void (*)(void))f, METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {METHOD(prefill),      METHOD(prefill_lse), METHOD(prefill_backward), METHOD(project_heads),
-                         METHOD(cache_append), METHOD(bind),        METHOD(connect),          {}};
+                         METHOD(cache_append), METHOD(bind),        METHOD(connect),          {"plain_args", plain_args, METH_O, nullptr},
+                         {}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_tkcall", nullptr, -1, methods};
 
 }  // namespace
