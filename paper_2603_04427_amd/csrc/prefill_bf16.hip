@@ -32,9 +32,9 @@
 //    each bf16 P^T operand adds up exactly the rounded probabilities that feed
 //    the value product, in place of 16 vector dot products per tile.
 //  * Causal masking only on tiles that cross a wave's diagonal; tiles above it
-//    are skipped. Workgroups are ordered heaviest (longest causal prefix) first
-//    over all KV sequences, the query blocks of one sequence on one XCD, or
-//    sequence by sequence where that serves K and V from the XCD's L2 (walk_order).
+//    are skipped. By the call's sizes, workgroups start longest walk first over
+//    all KV sequences, over those that their XCD owns, or sequence by sequence
+//    where that serves K and V from the XCD's L2 (walk_order).
 #include "tk_device.hpp"
 #include "tk_internal.hpp"
 

@@ -158,8 +158,8 @@ constexpr int prefill_most_groups(int r, int dv) {
 // causal, 12 heads, d_v 64, 21.2 / 21.7 (r 64: 23.9 / 28.7). Short walks: 5 x 207 causal
 // 8.8 / 12.0, 5 x 265 9.3 / 11.9, 28 heads over 4, 15 x 71 8.2 / 11.5 (two units x 2); 9 x
 // 178, r 16, 32 heads over 4 of d_v 64, 3 tiles 7.7 / 8.8; 32 heads, r 64, 5 x 94 6.8 / 8.8
-// (320 workgroups of two units x 3); 32 over 4 of d_v 64, r 64, 9 x 158 8.2 / 10.4; equal walks in 392 workgroups: 28 over 4, 7 x 131
-// over 508 16.2 / 20.0 (four units x 2).
+// (320 workgroups of two units x 3); 32 over 4 of d_v 64, r 64, 9 x 158 8.2 / 10.4; equal
+// walks in 392 workgroups: 28 over 4, 7 x 131 over 508 16.2 / 20.0 (four units x 2).
 constexpr PrefillForm prefill_form(const AttnSizes& s) {
     const int most = prefill_most_groups(s.r, s.dv);
     const bool pair = 4 * prefill_tile_lds(s.r, s.dv) <= 160 * 1024;  // two workgroups of two key groups share a CU

@@ -29,6 +29,7 @@ import torch
 from bwd_bound import admissible, check, exact_terms
 from gpu_cases import device, say
 from oracle import oracle as orc
+from test_gpu_prefill import ORDERS
 from synth import WORKLOADS, PrefillSpec, make_prefill, make_prefill_grad, with_shape
 
 pytestmark = pytest.mark.gpu
@@ -98,16 +99,24 @@ def test_backward_shapes_and_masks(shape):
     isolated(spec, structured=True)
 
 
-@pytest.mark.parametrize("r,dv,shape", [
-    (r, dv, shape) for r, dv in ((32, 64), (32, 128), (64, 64), (64, 128), (128, 128)) for shape in (
+WORKGROUP_WIDTHS = [(32, 64), (32, 128), (64, 64), (64, 128), (128, 128)]
+WORKGROUP_SHAPES = [  # units of 32 rows or keys; every form of both kernels at every width
+    (r, dv, shape) for r, dv in WORKGROUP_WIDTHS for shape in (
         (1, 4, 1, 300, 300, True),    # two units per workgroup in groups, walks over 4 heads
         (2, 6, 2, 257, 270, False),   # G = 3, ragged keys, no mask
-        (6, 48, 48, 100, 100, True),  # 1152 units: dQ by four; dK/dV by two on 32-row tiles, or by four
+        (6, 48, 48, 100, 100, True),  # 1152 units: dQ by four, or two at r + d_v 96; dK/dV by two on 32-row tiles, or by four
         (12, 72, 72, 97, 100, True),  # 3456 units: four per workgroup everywhere
     )] + [
     (32, 128, (1, 32, 8, 1050, 1250, True)),  # dQ in four units x 2 key groups
+    (32, 64, (1, 48, 8, 1050, 1290, True)),
     (64, 64, (1, 48, 8, 1050, 1290, True)),
-], ids=lambda x: "x".join(map(str, x)) if isinstance(x, tuple) else str(x))
+    (64, 128, (1, 48, 8, 1050, 1290, True)),
+    (128, 128, (1, 48, 8, 1050, 1290, True)),
+]
+
+
+@pytest.mark.parametrize("r,dv,shape", WORKGROUP_SHAPES,
+                         ids=lambda x: "x".join(map(str, x)) if isinstance(x, tuple) else str(x))
 def test_backward_workgroup_shapes(r, dv, shape):
     """The workgroup shapes of both kernels (units per workgroup x groups), every gradient.
 
@@ -117,6 +126,15 @@ def test_backward_workgroup_shapes(r, dv, shape):
     bar, against 1e-5 of it for i.i.d. inputs, which those shapes take."""
     B, Hq, Hkv, Sq, Sk, causal = shape
     isolated(with_shape(BASE, config_id=1050 + r, batch=B, h_q=Hq, h_kv=Hkv, seq_q=Sq, seq_k=Sk, causal=causal, r=r,
+                        d_v=dv), structured=r < 128)
+
+
+@pytest.mark.parametrize("r,dv", WORKGROUP_WIDTHS)
+@pytest.mark.parametrize("shape,order", ORDERS)
+def test_backward_workgroup_orders(shape, order, r, dv):
+    """Every gradient where dQ's workgroups take each of their orders; without a mask dK/dV's go by sequence."""
+    B, Hq, Hkv, Sq, Sk, causal = shape
+    isolated(with_shape(BASE, config_id=1060 + r, batch=B, h_q=Hq, h_kv=Hkv, seq_q=Sq, seq_k=Sk, causal=causal, r=r,
                         d_v=dv), structured=r < 128)
 
 

@@ -56,15 +56,19 @@ def test_shapes_and_masks(dtype, shape):
     gate(out, ref, dtype, str(spec))
 
 
-@pytest.mark.parametrize("r,dv", [(16, 64), (32, 128), (64, 64), (64, 128), (128, 128)])
-@pytest.mark.parametrize("shape", [
-    (1, 6, 2, 1050, 1050, True),   # 198 units of 32 rows: one unit per workgroup, G = 3, a ragged 17th tile
+WORKGROUP_WIDTHS = [(16, 64), (32, 128), (64, 64), (64, 128), (128, 128)]
+WORKGROUP_SHAPES = [  # units of 32 rows of one head; every form of every width (waves per tile x key groups)
+    (1, 6, 2, 1050, 1050, True),   # 198 units: one unit per workgroup, G = 3, a ragged 17th tile
     (1, 4, 1, 130, 190, False),    # 3 tiles: split in two at most
     (5, 20, 5, 70, 300, True),     # 300 units over a prefix: two per workgroup, key groups without a fifth tile
-    (9, 20, 5, 90, 530, True),     # 540 units, rows of equal walks: four units x 2 for wide values
-    (9, 20, 5, 90, 100, True),     # 540 units, 2 tiles
-    (4, 12, 12, 700, 1030, True),  # 1056 units on a causal ramp of 17 tiles
-], ids=lambda s: "x".join(map(str, s)))
+    (9, 20, 5, 90, 530, True),     # 540 units, rows of equal walks: two units x 2, four for wide values
+    (9, 20, 5, 90, 100, True),     # 540 units, 2 tiles: two units x 2 for narrow values, four units whole for wide
+    (4, 12, 12, 700, 1030, True),  # 1056 units on a causal ramp of 17 tiles: two units x 2, four for wide values
+]
+
+
+@pytest.mark.parametrize("r,dv", WORKGROUP_WIDTHS)
+@pytest.mark.parametrize("shape", WORKGROUP_SHAPES, ids=lambda s: "x".join(map(str, s)))
 def test_workgroup_shapes(shape, r, dv):
     """The bf16 workgroup shapes for few rows (waves per tile x key groups), every output."""
     B, Hq, Hkv, Sq, Sk, causal = shape
@@ -72,6 +76,25 @@ def test_workgroup_shapes(shape, r, dv):
     for structured in (False, True):
         out, ref = run_full(spec, structured)
         gate(out, ref, "bf16", f"{spec} structured={structured}")
+
+
+ORDERS = [  # four units whole, at every width; the order of their workgroups
+    ((4, 64, 8, 300, 300, True), "owned"),           # two head groups per KV sequence, 64 pairs: 10 ragged blocks each
+    ((12, 28, 4, 50, 60, True), "owned"),            # seven head groups, 336 pairs: an eighth ends inside a sequence
+    ((3, 28, 4, 50, 60, True), "by sequence"),       # 84 pairs: their number doesn't divide among the XCDs
+    ((25, 33, 33, 140, 140, False), "by sequence"),  # 825 pairs of 2 blocks, equal walks over more than one round
+    ((25, 33, 33, 60, 90, True), "longest first"),   # 825 pairs on a ramp
+]
+
+
+@pytest.mark.parametrize("r,dv", [(32, 64), *WORKGROUP_WIDTHS])
+@pytest.mark.parametrize("shape,order", ORDERS)
+def test_workgroup_orders(shape, order, r, dv):
+    """Every output where the workgroups take each of their orders."""
+    B, Hq, Hkv, Sq, Sk, causal = shape
+    spec = with_shape(BASE, config_id=770 + r, batch=B, h_q=Hq, h_kv=Hkv, seq_q=Sq, seq_k=Sk, causal=causal, r=r, d_v=dv)
+    out, ref = run_full(spec, structured=True)
+    gate(out, ref, "bf16", f"{spec} {order}")
 
 
 def test_gpt2_prefill_f32_full():

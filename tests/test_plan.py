@@ -221,6 +221,39 @@ def test_dkdv_form_of_measured_calls(plan, call, form):
     assert plan.dkdv_shape(*call) == form
 
 
+# calls of all sizes, to see which forms a width can take
+CALLS = [(B, Hkv * G, Hkv, Sq, Sk, causal) for B in (1, 3, 16) for Hkv in (1, 8, 32) for G in (1, 4, 7)
+         for Sq, Sk in ((1, 1), (60, 60), (60, 3000), (130, 190), (300, 300), (700, 1400), (1100, 1100), (2500, 2500),
+                        (8192, 8192)) for causal in (0, 1)]
+
+
+def test_prefill_shapes_of_the_parity_tests_cover_every_form_and_order(plan):
+    from test_gpu_prefill import ORDERS, WORKGROUP_SHAPES, WORKGROUP_WIDTHS
+    names = {"longest first": RANKED, "owned": OWNED, "by sequence": BY_SEQUENCE}
+    for r, dv in WORKGROUP_WIDTHS:
+        tested = {plan.form(*call[:5], r, dv, call[5]) for call in WORKGROUP_SHAPES}
+        assert tested | {41} == {plan.form(*call[:5], r, dv, call[5]) for call in CALLS}, (r, dv)
+    for r, dv in [(32, 64), *WORKGROUP_WIDTHS]:
+        for call, order in ORDERS:
+            assert plan.form(*call[:5], r, dv, call[5]) == 41, (call, r, dv)
+            assert plan.walks(*call[:5], r, dv, call[5], 3 if r <= 32 else 2) == names[order], (call, r, dv)
+    assert {order for _, order in ORDERS} == set(names)
+
+
+def test_backward_shapes_of_the_parity_tests_cover_every_form_and_order(plan):
+    from test_gpu_backward import ORDERS, WORKGROUP_SHAPES, WORKGROUP_WIDTHS
+    names = {"longest first": RANKED, "owned": OWNED, "by sequence": BY_SEQUENCE}
+    for width in WORKGROUP_WIDTHS:
+        for query in (plan.dq, plan.dkdv_shape):
+            tested = {query(*call[:5], r, dv, call[5]) for r, dv, call in WORKGROUP_SHAPES if (r, dv) == width}
+            assert tested == {query(*call[:5], *width, call[5]) for call in CALLS}, (width, query.__name__)
+        for call, order in ORDERS:
+            assert plan.dq(*call[:5], *width, call[5]) == 41, (call, width)
+            assert plan.walks(*call[:5], *width, call[5], 2) == names[order], (call, width)
+        whole = {call for call, _ in ORDERS if plan.dkdv_shape(*call[:5], *width, call[5]) == 4164}
+        assert {plan.dkdv(*call[:5], *width, call[5], 4) for call in whole} == {RANKED, BY_SEQUENCE}, width
+
+
 def test_projection_shapes_of_the_parity_test_cover_every_tile(plan):
     """Each entry of the GPU parity test runs the tile it is listed with, and every tile
     of the ladder has one."""
