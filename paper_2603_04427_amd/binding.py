@@ -151,22 +151,38 @@ class PreparedCall:
         self.args = args
         self.keep = keep  # tensors whose memory the pointers refer to
         self.result = keep[-1] if result is None else result
-        self._bound = self._bound_to = None
 
-    def _bind(self):
-        self._bound, self._bound_to = None, (self.fn, self.args)
-        native = _call or _load_call()
-        if self.fn is self._entry and self.name in _BOUND and native.plain_args(self.args):
-            try:
-                self._bound = native.bind(self.name, self.args)
-            except TypeError:  # ctypes says what is wrong with them
-                pass
+    @property
+    def fn(self):
+        return self._fn
+
+    @fn.setter
+    def fn(self, fn):
+        self._fn, self._bound, self._looked = fn, None, False
+
+    @property
+    def args(self):
+        return self._args
+
+    @args.setter
+    def args(self, args):
+        self._args, self._bound, self._looked = args, None, False
+
+    def _launch(self):
+        if not self._looked:
+            self._looked = True
+            native = _call or _load_call()
+            if self._fn is self._entry and self.name in _BOUND and native.plain_args(self._args):
+                try:
+                    self._bound = native.bind(self.name, self._args)
+                    return self._bound()
+                except TypeError:  # ctypes says what is wrong with them
+                    pass
+        return self._fn(*self._args)
 
     def __call__(self):
-        to = self._bound_to
-        if to is None or to[0] is not self.fn or to[1] is not self.args:
-            self._bind()
-        st = self._bound() if self._bound is not None else self.fn(*self.args)
+        bound = self._bound
+        st = self._launch() if bound is None else bound()
         if st != TK_OK:
             raise TkError(st, self.name)
         return self.result

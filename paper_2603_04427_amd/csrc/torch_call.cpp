@@ -28,6 +28,8 @@
 #include <c10/core/impl/TorchDispatchModeTLS.h>
 #include <c10/hip/HIPStream.h>
 
+#include <string.h>
+
 #include <memory>
 #include <string>
 #include <tuple>
@@ -292,13 +294,39 @@ PyObject* cache_append(PyObject*, PyObject* const* a, Py_ssize_t n) {
 
 // ------------------------------------------------------------------ bound calls
 
+PyObject* c_void_p() {
+    static PyObject* const type = [] {
+        THPObjectPtr ctypes(PyImport_ImportModule("ctypes"));
+        return ctypes ? PyObject_GetAttrString(ctypes.get(), "c_void_p") : nullptr;
+    }();
+    return type;
+}
+
+// A c_void_p's value, from its storage (its attribute would first become a Python integer).
+bool read_pointer(PyObject* o, void** out) {
+    Py_buffer at;
+    if (PyObject_GetBuffer(o, &at, PyBUF_SIMPLE) < 0) return false;
+    memcpy(out, at.buf, sizeof *out);
+    PyBuffer_Release(&at);
+    return true;
+}
+
 // One marshalled argument (an int, a float, None, or a ctypes object holding one),
-// converted as ctypes does: integers modulo the type's width.
+// converted as ctypes does: integers modulo the type's width, None and a c_void_p for
+// pointers alone.
 template <class T>
 bool convert(PyObject* o, T& out) {
     static PyObject* const value = PyUnicode_InternFromString("value");
     THPObjectPtr held;
-    if (o != Py_None && !PyLong_Check(o) && !PyFloat_Check(o)) {
+    if (o == Py_None || (PyObject*)Py_TYPE(o) == c_void_p()) {
+        if constexpr (std::is_pointer_v<T>) {
+            out = nullptr;
+            return o == Py_None || read_pointer(o, (void**)&out);
+        }
+        PyErr_SetString(PyExc_TypeError, "a number is needed");
+        return false;
+    }
+    if (!PyLong_Check(o) && !PyFloat_Check(o)) {
         held = PyObject_GetAttr(o, value);
         if (!held) return false;
         o = held.get();
@@ -318,26 +346,37 @@ bool convert(PyObject* o, T& out) {
     return true;
 }
 
-// An entry point called with a tuple's arguments: its status, or -1 with an error set
-// (`launch` false: they are only converted).
+// An entry point called with a tuple's arguments: its status, or -1 with an error set.
+// The tuple and its numbers cannot change, the value of a c_void_p can: that is read for
+// each call.
 struct Call {
     virtual ~Call() = default;
-    virtual int run(PyObject* args, bool launch) const = 0;
+    virtual bool take(PyObject* args) = 0;
+    virtual int run(PyObject* args) const = 0;
 };
 template <class... A>
 struct Bound : Call {
     tk_status (*fn)(A...);
+    std::tuple<A...> taken;
+    bool reread[sizeof...(A)];
     explicit Bound(tk_status (*f)(A...)) : fn(f) {}
-    int run(PyObject* args, bool launch) const override { return run(args, launch, std::index_sequence_for<A...>{}); }
-    template <size_t... I>
-    int run(PyObject* args, bool launch, std::index_sequence<I...>) const {
+    bool take(PyObject* args) override {
         if (PyTuple_GET_SIZE(args) != (Py_ssize_t)sizeof...(A)) {
             PyErr_SetString(PyExc_TypeError, "wrong number of arguments");
-            return -1;
+            return false;
         }
-        std::tuple<A...> v;
-        if (!(convert(PyTuple_GET_ITEM(args, I), std::get<I>(v)) && ...)) return -1;
-        if (!launch) return TK_OK;
+        return take(args, std::index_sequence_for<A...>{});
+    }
+    int run(PyObject* args) const override { return run(args, std::index_sequence_for<A...>{}); }
+    template <size_t... I>
+    bool take(PyObject* args, std::index_sequence<I...>) {
+        ((reread[I] = (PyObject*)Py_TYPE(PyTuple_GET_ITEM(args, I)) == c_void_p()), ...);
+        return (convert(PyTuple_GET_ITEM(args, I), std::get<I>(taken)) && ...);
+    }
+    template <size_t... I>
+    int run(PyObject* args, std::index_sequence<I...>) const {
+        std::tuple<A...> v = taken;
+        if (!((!reread[I] || convert(PyTuple_GET_ITEM(args, I), std::get<I>(v))) && ...)) return -1;
         NoGil nogil;
         return std::apply(fn, v);
     }
@@ -359,7 +398,7 @@ void bound_dealloc(PyObject* self) {
 }
 PyObject* bound_call(PyObject* self, PyObject*, PyObject*) {
     const BoundObject* b = (const BoundObject*)self;
-    const int st = b->call->run(b->args, true);
+    const int st = b->call->run(b->args);
     return st < 0 ? nullptr : PyLong_FromLong(st);
 }
 PyTypeObject BoundType = {PyVarObject_HEAD_INIT(nullptr, 0)};
@@ -388,7 +427,7 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
         call = call_of(g.project);
     else
         return PyErr_Format(PyExc_ValueError, "no entry point %s", name.c_str());
-    if (call->run(a[1], false) < 0) return nullptr;
+    if (!call->take(a[1])) return nullptr;
     BoundObject* o = PyObject_New(BoundObject, &BoundType);
     if (!o) return nullptr;
     o->call = call.release();
@@ -400,10 +439,7 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
 // (args): whether bind() reads them as ctypes would, each being exactly one of the
 // types that it converts
 PyObject* plain_args(PyObject*, PyObject* args) {
-    static PyObject* const pointer = [] {
-        THPObjectPtr ctypes(PyImport_ImportModule("ctypes"));
-        return ctypes ? PyObject_GetAttrString(ctypes.get(), "c_void_p") : nullptr;
-    }();
+    PyObject* const pointer = c_void_p();
     if (!pointer) return nullptr;
     bool plain = PyTuple_CheckExact(args);
     for (Py_ssize_t i = 0; plain && i < PyTuple_GET_SIZE(args); ++i) {
